@@ -10,7 +10,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(PKG, "libqwalk.so")
-SOURCES = ["qw_kernels.hip", "qw_stream_wg.hip", "qw_api.hip", "qw_batch.hip", "qw_surrogate.hip",
+SOURCES = ["qw_cone.hip", "qw_kernels.hip", "qw_stream_wg.hip", "qw_api.hip", "qw_batch.hip", "qw_surrogate.hip",
            "qw_graph.hip"]
 
 HIPCC_FLAGS = [

@@ -202,6 +202,12 @@ struct qw_walk {
     // at one parity of x - x0 on a ring): set by create and reset, cleared by
     // walk_set_state and inverse steps
     bool pure = false;
+    // a torus walk from one site, held as the square of its live sites (cone.t ==
+    // t; the boxes above are then unused): set by create and reset where the lattice
+    // and the options allow it, cleared by leave_cone
+    bool on_cone = false;
+    bool fourier = false;  // the coin is the 4-point Fourier matrix
+    Cone cone{};
     int emin[2] = {0, 0}, emax[2] = {0, 0};
     qw_options opt;
     // random broken links (walk_set_broken_links); rbl.step is filled per launch
@@ -376,6 +382,80 @@ double state_bytes_of(const qw_walk *w, int64_t sites) {
     return (double)sites * w->d * (w->prec == QW_C128 ? 16.0 : 8.0);
 }
 
+// whether a walk that starts now is held as the square of its live sites: the
+// default torus kernels and the light-cone window, every link intact.  Any of the
+// tuning options of the whole-lattice streaming kernels keeps those kernels.
+bool cone_allowed(const qw_walk *w, Cone *c) {
+    const qw_options &o = w->opt;
+    return w->dim == 2 && !w->rbl_on && o.window == 1 && (o.block_depth == 0 || o.block_depth >= 4) &&
+           o.prefetch_rows == 0 && o.stream_waves == 0 && o.block_order == 0 && o.stream_kernel == 0 &&
+           cone_fits(w->g, w->table, w->state_bytes, w->prec, c);
+}
+
+// From the square of live sites to the whole lattice (and its boxes): before
+// anything the square cannot hold -- a cone about to close around the torus,
+// broken links, other kernels asked for.
+int leave_cone(qw_walk *w) {
+    if (!w->on_cone) return QW_OK;
+    QW_HIP(launch_cone_expand(w->prec, w->table, cur_buf(w), w->cone, w->g, oth_buf(w), true, w->stream),
+           "state expansion kernel");
+    QW_HIP(launch_fill_zero(cur_buf(w), w->state_bytes, w->stream), "fill kernel");
+    w->cur ^= 1;
+    w->on_cone = false;
+    for (int ax = 0; ax < 2; ++ax) {
+        w->lo[ax] = -w->emax[ax];
+        w->hi[ax] = -w->emin[ax];
+        w->full[ax] = false;
+        normalise_axis(w, ax);
+    }
+    grow_forward(w, w->cone.t);
+    return QW_OK;
+}
+
+// Steps of the next launch on the square, of `left` up to the next norm check; 0:
+// the cone closes around the torus.  complex64 with the Grover or H (x) H coin:
+// whole groups of the steps the whole-lattice kernels take per launch, with a mark
+// at the end of each, so that values rounded as subnormals there are rounded here.
+int cone_steps(const qw_walk *w, int64_t left, uint32_t *marks) {
+    *marks = 0;
+    const int64_t room = std::min<int64_t>(left, w->cone.tmax - w->cone.t);
+    if (room == 0) return 0;
+    const int cap = cone_depth(w->coin_impl, false, w->cone, w->C, room,
+                               w->opt.block_depth ? w->opt.block_depth : cone_max_depth());
+    if (w->prec != QW_C64 || w->coin_impl == COIN_DENSE) return cap;
+    const int depth = w->opt.block_depth ? w->opt.block_depth : default_depth(w);
+    int kk = 0;
+    while (kk < left) {
+        const int g = w->g.Lx >= 64 ? fit_depth(w, (int)std::min<int64_t>(depth, left - kk), false) : 1;
+        if (kk + g > cap) break;
+        kk += g;
+        *marks |= 1u << (kk - 1);
+    }
+    return kk;
+}
+
+// kk steps on the square
+int step_cone(qw_walk *w, int kk, bool inverse, uint32_t marks = 0) {
+    const int64_t t = w->cone.t;
+    int64_t upd = 0;
+    for (int64_t s = 1; s <= kk; ++s) {
+        const int64_t side = inverse ? t - s + 1 : t + s;
+        upd += side * side * w->d;
+    }
+    const int64_t in_sites = (t + 1) * (t + 1), t1 = inverse ? t - kk : t + kk, out_sites = (t1 + 1) * (t1 + 1);
+    LaunchInfo li;
+    Timed tm(w, out_sites >= (int64_t)1 << 16);  // as stepK: large launches stamp their own events
+    QW_HIP(launch_cone_steps(w->prec, w->coin_impl, w->table, inverse, cur_buf(w), oth_buf(w), w->cone, kk, marks,
+                             inverse ? w->Cdag : w->C, w->stream, &li, tm.start(), tm.stop()),
+           "light-cone kernel");
+    tm.done(QW_KERNEL_STREAM2D, li, (double)upd, state_bytes_of(w, in_sites + out_sites));
+    w->cur ^= 1;
+    w->cone.t = (int32_t)t1;
+    w->launches++;
+    w->updates += upd;
+    return QW_OK;
+}
+
 int step1(qw_walk *w) {
     const int64_t in_sites = box_sites(state_box(w));
     grow_forward(w, 1);
@@ -488,6 +568,19 @@ int step1_rbl(qw_walk *w) {
 
 int run_forward(qw_walk *w, int64_t n) {
     if (n <= 0) return QW_OK;
+    if (w->on_cone) {
+        uint32_t marks;
+        while (n > 0) {
+            const int kk = cone_steps(w, n, &marks);
+            if (kk == 0) break;
+            const int rc = step_cone(w, kk, false, marks);
+            if (rc) return rc;
+            n -= kk;
+        }
+        if (n == 0) return QW_OK;
+        const int rc = leave_cone(w);  // the cone closes around the torus
+        if (rc) return rc;
+    }
     if (w->rbl_on) {
         // rings held whole: all n steps in one launch; tori: K steps per launch,
         // each level drawing its step's links inside the streaming kernel;
@@ -586,7 +679,20 @@ int run_forward(qw_walk *w, int64_t n) {
     return QW_OK;
 }
 
+// the fp64 norm into the scratch area
+hipError_t norm_of(qw_walk *w) {
+    return w->on_cone ? launch_cone_norm(w->prec, w->table, cur_buf(w), w->cone, w->g, w->scr, w->stream)
+                      : launch_norm(w->prec, cur_buf(w), w->g, psi_box(w), w->scr, w->stream);
+}
+
 int norm_check(qw_walk *w) {
+    if (w->on_cone) {
+        QW_HIP(norm_of(w), "norm kernel");
+        QW_HIP(launch_cone_renorm(w->prec, cur_buf(w), w->cone, w->g, w->opt.renorm_tol, w->scr, w->stream),
+               "renorm kernel");
+        w->checks++;
+        return QW_OK;
+    }
     const Box pb = psi_box(w);
     QW_HIP(launch_norm(w->prec, cur_buf(w), w->g, pb, w->scr, w->stream), "norm kernel");
     QW_HIP(launch_renorm(w->prec, cur_buf(w), w->g, state_box(w), w->opt.renorm_tol, w->scr, w->stream),
@@ -687,6 +793,7 @@ int configure(qw_walk *w, const qw_lattice *l, const qw_coin *coin, const double
     if (l->d == 4 && coin->kind == QW_COIN_GROVER) w->coin_impl = COIN_GROVER4;
     else if (l->d == 4 && coin->kind == QW_COIN_HADAMARD2) w->coin_impl = COIN_HH4;
     else w->coin_impl = COIN_DENSE;
+    w->fourier = l->d == 4 && coin->kind == QW_COIN_FOURIER;
     w->stream = (hipStream_t)stream;
     w->opt.block_depth = 0;
     w->opt.window = 1;
@@ -707,14 +814,29 @@ int configure(qw_walk *w, const qw_lattice *l, const qw_coin *coin, const double
     return QW_OK;
 }
 
-// The start state |x0> (x) psi0 in the walk's buffers (both cleared) and a
-// cleared scratch area: fill and place kernels on the walk's stream.
-hipError_t start_state(qw_walk *w, const double *psi0) {
+// |x0> (x) psi0 in buffer 0: on the square of live sites where the walk may run
+// there (nothing outside the square is read, so nothing is cleared), else in
+// both buffers cleared.
+hipError_t place_state(qw_walk *w, const double *psi0) {
+    w->on_cone = cone_allowed(w, &w->cone);
+    if (w->on_cone) {
+        w->cone.t = 0;
+        w->cone.fourier = w->fourier;
+        w->cone.x0 = (int32_t)w->x0[0];
+        w->cone.y0 = (int32_t)w->x0[1];
+        return launch_cone_place(w->prec, w->buf[0], w->cone, psi0, w->stream);
+    }
     hipError_t e1 = launch_fill_zero(w->buf[0], w->state_bytes, w->stream);
     hipError_t e2 = launch_fill_zero(w->buf[1], w->state_bytes, w->stream);
-    hipError_t e3 = launch_fill_zero(w->scr, sizeof(Scratch), w->stream);
-    hipError_t e4 = launch_place(w->prec, w->buf[0], w->g, w->x0[0], w->x0[1], psi0, w->stream);
-    return e1 != hipSuccess ? e1 : (e2 != hipSuccess ? e2 : (e3 != hipSuccess ? e3 : e4));
+    hipError_t e3 = launch_place(w->prec, w->buf[0], w->g, w->x0[0], w->x0[1], psi0, w->stream);
+    return e1 != hipSuccess ? e1 : (e2 != hipSuccess ? e2 : e3);
+}
+
+// The start state and a cleared scratch area: kernels on the walk's stream.
+hipError_t start_state(qw_walk *w, const double *psi0) {
+    const hipError_t e1 = launch_fill_zero(w->scr, sizeof(Scratch), w->stream);
+    const hipError_t e2 = place_state(w, psi0);
+    return e1 != hipSuccess ? e1 : e2;
 }
 
 int create_common(const qw_lattice *l, const qw_coin *coin, const double *psi0, const int64_t *x0, int32_t prec,
@@ -820,9 +942,7 @@ int walk_reset(qw_walk_t w, const double *psi0, const int64_t *x0) {
     w->cur = 0;
     w->t = 0;
     w->since_check = 0;
-    QW_HIP(launch_fill_zero(w->buf[0], w->state_bytes, w->stream), "fill kernel");
-    QW_HIP(launch_fill_zero(w->buf[1], w->state_bytes, w->stream), "fill kernel");
-    QW_HIP(launch_place(w->prec, w->buf[0], w->g, w->x0[0], w->x0[1], psi0, w->stream), "place kernel");
+    QW_HIP(place_state(w, psi0), "start state kernels");
     return QW_OK;
 }
 
@@ -866,6 +986,20 @@ int walk_step_inverse(qw_walk_t w, int64_t T) {
     if (w->rbl_on) return fail(QW_EINVAL, "inverse steps are not available while links break at random");
     DeviceGuard dg(w->device);
     w->pure = false;
+    if (w->on_cone) {
+        // the cone shrinks again; what a step of U^-1 leaves outside it is rounding
+        // noise around exact zeros
+        while (T > 0 && w->cone.t > 0) {
+            const int kk = cone_depth(w->coin_impl, true, w->cone, w->Cdag, std::min<int64_t>(T, w->cone.t), cone_max_depth());
+            const int rc = step_cone(w, kk, true);
+            if (rc) return rc;
+            w->t -= kk;
+            T -= kk;
+        }
+        if (T == 0) return QW_OK;
+        const int rc = leave_cone(w);
+        if (rc) return rc;
+    }
     for (int64_t s = 0; s < T; ++s) {
         grow_inverse(w, 1);
         const Box b = state_box(w);
@@ -897,8 +1031,10 @@ int walk_probabilities(qw_walk_t w, double *out, int32_t out_on_device) {
         P = w->pbuf;
     }
     const Box pb = psi_box(w);
-    if (box_sites(pb) < w->g.ps) QW_HIP(launch_fill_zero(P, pbytes, w->stream), "fill kernel");
-    if (w->rbl_on && w->t > 0)
+    if (!w->on_cone && box_sites(pb) < w->g.ps) QW_HIP(launch_fill_zero(P, pbytes, w->stream), "fill kernel");
+    if (w->on_cone)
+        QW_HIP(launch_cone_prob(w->prec, w->table, cur_buf(w), w->cone, w->g, P, w->stream), "probability kernel");
+    else if (w->rbl_on && w->t > 0)
         QW_HIP(launch_prob_norm_rbl(w->prec, cur_buf(w), w->g, pb, P, w->scr, pending_links(w), w->stream),
                "probability kernel");
     else
@@ -914,7 +1050,7 @@ int walk_norm(qw_walk_t w, double *out) {
     if (!w) return fail(QW_EINVAL, "walk handle is NULL");
     if (!out) return fail(QW_EINVAL, "output pointer is NULL");
     DeviceGuard dg(w->device);
-    QW_HIP(launch_norm(w->prec, cur_buf(w), w->g, psi_box(w), w->scr, w->stream), "norm kernel");
+    QW_HIP(norm_of(w), "norm kernel");
     QW_HIP(hipMemcpyAsync(out, &w->scr->norm, sizeof(double), hipMemcpyDeviceToHost, w->stream), "copy of the norm");
     QW_HIP(hipStreamSynchronize(w->stream), "stream synchronise");
     return QW_OK;
@@ -933,7 +1069,8 @@ int walk_get_state(qw_walk_t w, double *out, int32_t out_on_device) {
             return fail(QW_ENOMEM, "hipMalloc of the state staging buffer failed: %s", hipGetErrorString(e));
         }
     }
-    hipError_t e = (w->rbl_on && w->t > 0)
+    hipError_t e = w->on_cone ? launch_cone_expand(w->prec, w->table, cur_buf(w), w->cone, w->g, dst, false, w->stream)
+                   : (w->rbl_on && w->t > 0)
                        ? launch_get_state_rbl(w->prec, cur_buf(w), w->g, dst, pending_links(w), w->stream)
                        : launch_get_state(w->prec, cur_buf(w), w->g, dst, w->stream);
     if (e == hipSuccess && !out_on_device) {
@@ -980,6 +1117,7 @@ int walk_set_state(qw_walk_t w, const double *in, int32_t in_on_device) {
     }
     w->cur ^= 1;
     w->pure = false;
+    w->on_cone = false;
     w->full[0] = w->full[1] = true;
     w->since_check = 0;
     return QW_OK;
@@ -1008,6 +1146,11 @@ int walk_set_options(qw_walk_t w, const qw_options *o) {
         return fail(QW_EINVAL, "stream_kernel must be 0, 1, 2 or 3 (got %d)", o->stream_kernel);
     w->opt = *o;
     w->since_check = 0;
+    Cone c;
+    if (w->on_cone && !cone_allowed(w, &c)) {
+        DeviceGuard dg(w->device);
+        return leave_cone(w);
+    }
     return QW_OK;
 }
 
@@ -1033,6 +1176,11 @@ int walk_set_broken_links(qw_walk_t w, double p, uint64_t seed, uint64_t realiza
     L.key1 = (uint32_t)(seed >> 32);
     L.realization = (uint32_t)realization;
     L.step = -1;
+    if (w->on_cone && (L.thr != 0 || L.walls != 0)) {
+        DeviceGuard dg(w->device);
+        const int rc = leave_cone(w);
+        if (rc) return rc;
+    }
     w->rbl = L;
     w->rbl_on = L.thr != 0 || L.walls != 0;
     return QW_OK;
@@ -1049,6 +1197,11 @@ int walk_set_reflecting_walls(qw_walk_t w, int32_t on) {
     }
     L.walls = on;
     L.step = -1;
+    if (w->on_cone && (L.thr != 0 || L.walls != 0)) {
+        DeviceGuard dg(w->device);
+        const int rc = leave_cone(w);
+        if (rc) return rc;
+    }
     w->rbl = L;
     w->rbl_on = L.thr != 0 || L.walls != 0;
     return QW_OK;

@@ -150,5 +150,44 @@ hipError_t launch_get_state(int prec, const void *state, const Geom &g, double *
                             hipStream_t s);
 hipError_t launch_set_state(int prec, void *state, const Geom &g, const double *in,
                             Scratch *scr, hipStream_t s);
+// scratch->norm = sum of the first n partials (fixed order)
+hipError_t launch_reduce_final(Scratch *scr, int n, hipStream_t s);
+
+// ---- torus walks from one site on the square of their live sites (qw_cone.hip) ----
+// psi_t as a (t + 1) x (t + 1) square: 8 planes (Re, Im of component 0, 1, 2, 3),
+// ps elements apart, rows of ld elements; t <= tmax = min(Lx, Ly) / 2
+struct Cone {
+    int64_t ps;
+    int32_t ld, tmax, t;
+    int32_t x0, y0;  // the start site
+    int32_t fourier; // the coin is the 4-point Fourier matrix
+};
+struct ConePsi0 {
+    double re[4], im[4];
+};
+// whether a walk on this lattice and table can be held so in a buffer of
+// state_bytes; fills ps, ld, tmax
+bool cone_fits(const Geom &g, int table, size_t state_bytes, int prec, Cone *c);
+int cone_max_depth();  // most steps of one launch
+// steps the next launch should take, of `left` that remain and at most max_depth
+int cone_depth(int coin_impl, bool inverse, const Cone &c, const CoinF64 &C, int64_t left, int max_depth);
+// psi_0 into the square of t = 0
+hipError_t launch_cone_place(int prec, void *state, const Cone &c, const double *psi0, hipStream_t s);
+// kk steps (of U, or U^-1 with C = C^dagger) from the state of time c.t: kk <=
+// cone_max_depth(), c.t + kk <= c.tmax, or kk <= c.t for the inverse.  marks: bit s
+// set where the kernels of the whole lattice would store the state after step s + 1
+// (the coins that keep a factor 2 per step out multiply it back there, which
+// rounds subnormal values); the launch's end is always one
+hipError_t launch_cone_steps(int prec, int coin_impl, int table, bool inverse, const void *in, void *out, const Cone &c,
+                             int kk, uint32_t marks, const CoinF64 &C, hipStream_t s, LaunchInfo *info, hipEvent_t ev_start,
+                             hipEvent_t ev_stop);
+// P(x) over the whole lattice
+hipError_t launch_cone_prob(int prec, int table, const void *state, const Cone &c, const Geom &g, double *P, hipStream_t s);
+// the fp64 norm into scratch->norm; the conditional rescale, as launch_renorm
+hipError_t launch_cone_norm(int prec, int table, const void *state, const Cone &c, const Geom &g, Scratch *scr, hipStream_t s);
+hipError_t launch_cone_renorm(int prec, void *state, const Cone &c, const Geom &g, double tol, Scratch *scr, hipStream_t s);
+// the whole lattice: the pre-shift state (full) or psi as complex128 (!full)
+hipError_t launch_cone_expand(int prec, int table, const void *state, const Cone &c, const Geom &g, void *out, bool full,
+                              hipStream_t s);
 
 }  // namespace qw

@@ -1385,6 +1385,11 @@ hipError_t launch_prob_norm(int prec, const void *state, const Geom &g, const Bo
     return hipGetLastError();
 }
 
+hipError_t launch_reduce_final(Scratch *scr, int n, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, s, (const double *)scr->partial, n, &scr->norm);
+    return hipGetLastError();
+}
+
 hipError_t launch_norm(int prec, const void *state, const Geom &g, const Box &b, Scratch *scr, hipStream_t s) {
     return launch_prob_norm(prec, state, g, b, nullptr, scr, s);
 }

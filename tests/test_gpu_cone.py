@@ -1,0 +1,127 @@
+"""Torus walks held as the square of their live sites, against the kernels of the
+whole lattice (asked for with stream_kernel) and the oracle.
+
+Every live amplitude is the same expression whichever kernel computes it, so
+states agree bit for bit (in complex64 below the smallest normal number too, where it
+matters at which steps the levels' powers of two are multiplied back: a difference
+there climbs, one rounding at a time).  The Fourier coin's complex128 butterflies and the inverse walk (which drops the rounding noise outside the
+shrinking cone) agree to the sum of their roundings: T steps of at most 8 epsilon.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1003_3779_amd import inputs, qwalk
+
+pytestmark = pytest.mark.gpu
+
+EPS = {qwalk.QW_C128: 2.0 ** -53, qwalk.QW_C64: 2.0 ** -24}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    qwalk.load()
+    yield
+
+
+def _run(ext, table, kind, psi0, x0, plan, prec, dense=None, **opts):
+    w = qwalk.Walk(ext, getattr(inputs, table), kind, psi0, x0, prec=prec, dense=dense)
+    w.set_options(renorm_every=0, **opts)
+    for n in plan:
+        (w.step if n >= 0 else w.step_inverse)(abs(n))
+    out = w.probabilities(), w.get_state(), w.norm(), w.time()
+    w.destroy()
+    return out
+
+
+@pytest.mark.parametrize("prec", [qwalk.QW_C128, qwalk.QW_C64])
+@pytest.mark.parametrize("table", ["PAIR", "EQ8", "DIAG"])
+@pytest.mark.parametrize("kind", [qwalk.GROVER, qwalk.HADAMARD2, qwalk.FOURIER, qwalk.DENSE])
+@pytest.mark.parametrize("ext,plans", [
+    # the smallest torus; the last step before the seam, on it and past it; every remainder of 16
+    ((32, 33), ([0], [1], [15], [16], [17], [3, 5, 20])),
+    ((130, 97), ([47], [48], [49], [31, 9, 7, 1], [40, -13, 6], [20, -20], [9, -12])),
+    # squares past what the small-square kernel takes, strips and segments with remainders
+    ((905, 870), ([433], [417, -30])),
+])
+def test_cone_equals_whole_lattice(prec, table, kind, ext, plans):
+    rng = np.random.default_rng([ext[0], kind, prec, len(table)])
+    dense = inputs.haar_unitary(rng, 4) if kind == qwalk.DENSE else None
+    psi0 = inputs.haar_state(rng, 4)
+    x0 = (int(rng.integers(0, ext[0])), int(rng.integers(0, ext[1])))
+    for plan in plans:
+        P, psi, n, t = _run(ext, table, kind, psi0, x0, plan, prec, dense)
+        Pr, ref, nr, tr = _run(ext, table, kind, psi0, x0, plan, prec, dense, stream_kernel=1)
+        assert t == tr == sum(plan)
+        steps = sum(abs(k) for k in plan)
+        same = not (kind == qwalk.FOURIER and prec == qwalk.QW_C128) and min(plan) >= 0
+        tol = 0.0 if same else 8 * steps * EPS[prec]
+        assert np.max(np.abs(psi - ref)) <= tol, plan
+        assert np.max(np.abs(P - Pr)) <= max(2 * tol, 4 * EPS[qwalk.QW_C128]), plan
+        assert abs(n - nr) <= max(2 * tol, 64 * EPS[qwalk.QW_C128]), plan
+
+
+@pytest.mark.parametrize("table", ["PAIR", "EQ8", "DIAG"])
+def test_cone_against_oracle_on_the_seam(table):
+    """Both axes' outermost points meet at t = L / 2 (where P sums them)."""
+    L, T = 64, 32
+    psi0 = inputs.haar_state(np.random.default_rng(5), 4)
+    C = oracle.coin(oracle.GROVER, 4)
+    P, psi, n, _ = _run((L, L), table, qwalk.GROVER, psi0, (60, 3), [T], qwalk.QW_C128)
+    ref = oracle.walk(L, L, getattr(inputs, table), C, (60, 3), psi0, T)
+    assert np.max(np.abs(P - oracle.prob(ref))) <= 1e-12
+    assert np.max(np.abs(psi - np.transpose(ref, (2, 0, 1)))) <= 1e-12
+
+
+def test_leaving_the_cone():
+    """What the square cannot hold takes the walk to the whole lattice, unchanged:
+    other kernels asked for, links that break, a state set by the caller."""
+    ext, x0 = (80, 70), (11, 60)
+    psi0 = inputs.haar_state(np.random.default_rng(6), 4)
+    ref = _run(ext, "PAIR", qwalk.GROVER, psi0, x0, [30], qwalk.QW_C128, stream_kernel=1)[1]
+    w = qwalk.Walk(ext, inputs.PAIR, qwalk.GROVER, psi0, x0)
+    w.step(20)
+    before = w.get_state()
+    w.set_options(block_depth=1)
+    assert np.array_equal(w.get_state(), before)
+    w.step(10)
+    assert np.array_equal(w.get_state(), ref)
+    w.set_options(block_depth=0)
+    w.reset(psi0, x0)
+    w.step(20)
+    state = w.get_state()
+    assert np.array_equal(state, before)
+    w.set_state(state)
+    w.step(10)
+    assert np.array_equal(w.get_state(), ref)
+    w.reset(psi0, x0)
+    w.set_broken_links(1.0, seed=3)
+    w.step(6)
+    P = w.probabilities()
+    assert abs(P[x0[1], x0[0]] - 1.0) <= 1e-14      # every link broken: the walker stays
+    w.set_options()
+    w.reset(psi0, x0)
+    w.set_broken_links(0.0)
+    w.step(30)
+    assert np.array_equal(w.get_state(), ref)
+    w.destroy()
+
+
+def test_cone_norm_checks_complex64():
+    """The rescales of complex64 walks: a check every 64 steps, as on the whole lattice."""
+    psi0 = inputs.haar_state(np.random.default_rng(7), 4)
+    res = []
+    for opts in ({}, {"stream_kernel": 1}):
+        w = qwalk.Walk((600, 610), inputs.PAIR, qwalk.HADAMARD2, psi0, (3, 4), prec=qwalk.QW_C64)
+        w.set_options(**opts)
+        w.step(290)
+        st = w.stats()
+        res.append((w.probabilities(), w.norm(), st.renorm_checks, st.renorms))
+        w.destroy()
+    assert res[0][2] == res[1][2] == 290 // 64 and res[0][3] == res[1][3]
+    assert np.max(np.abs(res[0][0] - res[1][0])) <= 2 * EPS[qwalk.QW_C64] * np.max(res[1][0])
+    assert abs(res[0][1] - 1.0) <= 1e-6
