@@ -206,6 +206,7 @@ struct qw_walk {
     // t; the boxes above are then unused): set by create and reset where the lattice
     // and the options allow it, cleared by leave_cone
     bool on_cone = false;
+    int norm_parts = 0;    // partial sums of the norm that the latest launch on the square left (norm_check)
     bool fourier = false;  // the coin is the 4-point Fourier matrix
     Cone cone{};
     int emin[2] = {0, 0}, emax[2] = {0, 0};
@@ -435,7 +436,7 @@ int cone_steps(const qw_walk *w, int64_t left, uint32_t *marks) {
 }
 
 // kk steps on the square
-int step_cone(qw_walk *w, int kk, bool inverse, uint32_t marks = 0) {
+int step_cone(qw_walk *w, int kk, bool inverse, uint32_t marks = 0, bool norm = false) {
     const int64_t t = w->cone.t;
     int64_t upd = 0;
     for (int64_t s = 1; s <= kk; ++s) {
@@ -446,11 +447,13 @@ int step_cone(qw_walk *w, int kk, bool inverse, uint32_t marks = 0) {
     LaunchInfo li;
     Timed tm(w, out_sites >= (int64_t)1 << 16);  // as stepK: large launches stamp their own events
     QW_HIP(launch_cone_steps(w->prec, w->coin_impl, w->table, inverse, cur_buf(w), oth_buf(w), w->cone, kk, marks,
-                             inverse ? w->Cdag : w->C, w->stream, &li, tm.start(), tm.stop()),
+                             inverse ? w->Cdag : w->C, w->stream, &li, norm ? w->scr : nullptr, tm.start(),
+                             tm.stop()),
            "light-cone kernel");
     tm.done(QW_KERNEL_STREAM2D, li, (double)upd, state_bytes_of(w, in_sites + out_sites));
     w->cur ^= 1;
     w->cone.t = (int32_t)t1;
+    w->norm_parts = li.norm_parts;
     w->launches++;
     w->updates += upd;
     return QW_OK;
@@ -569,11 +572,14 @@ int step1_rbl(qw_walk *w) {
 int run_forward(qw_walk *w, int64_t n) {
     if (n <= 0) return QW_OK;
     if (w->on_cone) {
+        const int64_t all = n;
         uint32_t marks;
         while (n > 0) {
             const int kk = cone_steps(w, n, &marks);
             if (kk == 0) break;
-            const int rc = step_cone(w, kk, false, marks);
+            // the last launch before a norm check sums the norm as it stores
+            const bool check = w->opt.renorm_every > 0 && kk == n && w->since_check + all >= w->opt.renorm_every;
+            const int rc = step_cone(w, kk, false, marks, check);
             if (rc) return rc;
             n -= kk;
         }
@@ -687,7 +693,8 @@ hipError_t norm_of(qw_walk *w) {
 
 int norm_check(qw_walk *w) {
     if (w->on_cone) {
-        QW_HIP(norm_of(w), "norm kernel");
+        if (w->norm_parts > 0) QW_HIP(launch_reduce_final(w->scr, w->norm_parts, w->stream), "norm kernel");
+        else QW_HIP(norm_of(w), "norm kernel");
         QW_HIP(launch_cone_renorm(w->prec, cur_buf(w), w->cone, w->g, w->opt.renorm_tol, w->scr, w->stream),
                "renorm kernel");
         w->checks++;

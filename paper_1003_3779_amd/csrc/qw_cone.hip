@@ -23,16 +23,25 @@
 #include "qw_device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace qw {
 namespace {
 
 constexpr int kConeMinSide = 32;  // smaller tori stay on the whole lattice: their cone closes within a launch or two
-constexpr int kConeWaves = 2;     // waves per SIMD a launch aims at
+constexpr int kConeWaves = 1;     // waves per SIMD a one-stage launch aims at (2: 7.3 / 30.9 ms, the halo rows of shorter segments)
+// launches of more than kK steps: levels a stage, stages, rows a group.  Four stages of
+// 8 levels, 4096^2 Grover complex128 / 16384^2 H (x) H complex64: 5.71 / 27.9 ms a
+// walk; two of 16 5.74 / 29.3, four with twice the columns a lane and one row a group 6.8 /
+// 35.4, one-stage launches of 16 throughout 6.98 / 29.9.  Waves per SIMD: 2 (1: 6.6 / 33.5,
+// 3: 6.0 / 29.2)
+constexpr int kDeepKL = 8, kDeepNS = 4, kDeepNR = 2;
+template <typename R> constexpr int kDeepM = sizeof(R) == 8 ? 2 : 4;  // and columns a lane
+constexpr int kDeepSide = 700;  // squares from this side on take them (400 and 1200: the same within 1 %)
 constexpr int kConeMinRows = 8;   // shortest segment
 constexpr int kConeTilesPerCu = 1;  // a square of at most so many tiles per compute unit takes the tile kernel
 template <bool CPLX> constexpr int kTileDepth = CPLX ? 8 : 16;  // steps of a launch there
-constexpr int kK = 16;  // levels of a launch (fewer: the run-time count of the PART kernels)
+constexpr int kK = 16;  // most levels of a one-stage launch
 
 __host__ __device__ constexpr int cone_di(int table, int c) {
     return table == TABLE_DIAG ? ((c & 1) == 0) : (table == TABLE_PAIR ? (c == 0 || c == 2) : c < 2);
@@ -50,11 +59,12 @@ struct ConeArgs {
     int64_t ps;  // plane stride, elements
     int ld;      // row stride
     int t;       // time of the input
-    int kk;      // steps of this launch (kK unless PART)
+    int kk;      // steps of this launch
     int rows;    // rows of the launch's output that its segments share out
     int cols;    // columns of the output
     int nstrips, nseg, seg_rows;
     double unscale;  // 2^-(levels since the last mark) (coins that keep their factor 1/2 out)
+    double *partial; // non-null: each tile's (tile kernel: block's) sum of the squares it stores, in fp64
     uint32_t marks;  // bit s: multiply the factors back after level s too
 };
 
@@ -150,63 +160,81 @@ template <typename R, int COIN, int NP> __device__ __forceinline__ void site_coi
 // The factor by which level s multiplies its outputs back: 2^-(levels since the
 // last mark) at a mark, else 1.
 __device__ __forceinline__ bool mark_at(uint32_t marks, int s) { return (marks >> s) & 1u; }
+// the marks that are not at the end of a stage of KL levels
+template <int KL> __device__ __forceinline__ uint32_t inner_marks(uint32_t marks) {
+    constexpr uint32_t ends = KL == 16 ? 0x80008000u : 0x80808080u;
+    return marks & ~ends;
+}
 template <typename R> __device__ __forceinline__ R mark_scale(uint32_t marks, int s) {
     const uint32_t below = marks & ((1u << s) - 1u);
     const int n = below ? s - (31 - __builtin_clz(below)) : s + 1;
     return (R)1 / (R)(1u << n);
 }
 
+__device__ __forceinline__ double wave_sum64(double v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
 template <typename R, int M> struct alignas(sizeof(R) * M) VecR {
     R v[M];
 };
 
-// kk steps of the square.  One wave holds 64 * M columns (M per lane) and streams
-// along I; level s of row I needs rows I and I - 1 of the level before only, so
-// every level works on the row that has just arrived and keeps, per lane, the
+// kk steps of the square.  A wave holds 64 * M columns (M per lane) and streams along
+// I; level s of row I needs rows I and I - 1 of the level before only, so every
+// level works on the rows that have just arrived (NR of them) and keeps, per lane, the
 // previous row of the two components that move along I -- no lag between levels
 // and half the window of a kernel whose moves go both ways.  The two that move
-// along J take one lane exchange per M columns.  A strip gives 64 * M - kK
-// columns, a segment of S rows reads S + kk - 1.  INV: the inverse step,
-// psi_{t-1} = C^dagger S^-1 psi_t, the same moves mirrored (rows descending,
-// values from the right).  CPLX: complex lanes (any coin); else one real part
-// per wave (real coins: Re and Im evolve alone), half the registers.
-template <typename R, int M, int NR, int TABLE, int COIN, bool CPLX, bool INV, bool PART>
-__global__ __launch_bounds__(256, kConeWaves) void k_cone(const R *__restrict__ in, R *__restrict__ out, ConeArgs A, CoinR<R> C,
-                                              int xcd_order) {
+// along J take one lane exchange per M columns.  INV: the inverse step, psi_{t-1} =
+// C^dagger S^-1 psi_t, the same moves mirrored (rows descending, values from the
+// right).  CPLX: complex lanes (any coin); else one real part per wave (real coins:
+// Re and Im evolve alone), half the registers.
+//
+// NS waves share a tile: each runs KL levels and hands its rows to the next through
+// LDS a group later (two buffers, one barrier per group), so a launch of NS KL
+// levels holds the window of KL per wave and the state crosses HBM once.  A strip
+// gives 64 M - NS KL columns; a segment of S rows reads S + kk - 1, of which level s
+// works from row s on (in stream order: the rows before feed nothing).
+template <typename R, int KL, int NS, int M, int NR, int TABLE, int COIN, bool CPLX, bool INV>
+__global__ __launch_bounds__(256, 2) void k_cone(const R *__restrict__ in, R *__restrict__ out, ConeArgs A, CoinR<R> C) {
     constexpr int NP = CPLX ? 2 : 1;  // real parts per lane
-    constexpr int TW = 64 * M - kK;
+    constexpr int K = KL * NS, TW = 64 * M - K;
     constexpr bool kScaled = !INV && COIN != COIN_DENSE;
-    static_assert(kK % M == 0, "strips start at multiples of M");
+    static_assert(K % M == 0, "strips start at multiples of M");
+    static_assert(NS == 1 || NS == 2 || NS == 4, "a block's four waves are whole tiles");
+    using V = VecR<R, M>;
+    __shared__ V hand[NS > 1 ? 4 / NS * (NS - 1) * 2 * NR * 4 * NP * 64 : 1];  // [tile][stage][buffer][row][plane][lane]
     const int lane = threadIdx.x & 63;
+    // the hardware deals blocks to the 8 XCDs in turn: each XCD takes a contiguous
+    // range of (segment, strip) pairs, whose halos then meet in its L2
     int lb = blockIdx.x;
-    if (xcd_order) {
-        // the hardware deals blocks to the 8 XCDs in turn: each XCD takes a contiguous
-        // range of (segment, strip) pairs, whose halos then meet in its L2
+    {
         const int nb = gridDim.x, xcd = lb & 7, i = lb >> 3, per = nb >> 3, rem = nb & 7;
         lb = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + i;
     }
-    int wv = __builtin_amdgcn_readfirstlane(lb * 4 + (int)(threadIdx.x >> 6));
-    const int strip = wv % A.nstrips;
-    wv /= A.nstrips;
-    const int seg = wv % A.nseg, part = CPLX ? 0 : wv / A.nseg;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int stage = w % NS, tile = __builtin_amdgcn_readfirstlane(lb * (4 / NS) + w / NS);
+    const int strip = tile % A.nstrips, rest = tile / A.nstrips;
+    const int seg = rest % A.nseg, part = rest / A.nseg;
     const int r0 = seg * A.seg_rows;
-    if (part > 1 || (CPLX && wv >= A.nseg) || r0 >= A.rows) return;  // wave-uniform; no barriers in this kernel
-    const int r1 = min(A.rows, r0 + A.seg_rows);                     // own rows [r0, r1)
-    const int t = A.t, kk = PART ? A.kk : kK;
+    const bool active = part < (CPLX ? 1 : 2) && r0 < A.rows;
+    if (NS == 1 && !active) return;               // wave-uniform; one stage has no barriers
+    const int r1 = min(A.rows, r0 + A.seg_rows);  // own rows [r0, r1)
+    const int t = A.t, kk = A.kk;
     const int c0 = strip * TW;
-    const int col = c0 + lane * M - (INV ? 0 : kK);  // this lane's first column
+    const int col = c0 + lane * M - (INV ? 0 : K);  // this lane's first column
     const bool lane_in = col >= 0 && col <= t;
     const int lcol = lane_in ? col : 0;
     bool ok[M];
 #pragma unroll
     for (int m = 0; m < M; ++m) ok[m] = lane_in && col + m <= t;
-    const bool own = INV ? (lane * M < TW && col < A.cols) : (lane * M >= kK && col < A.cols);
+    const bool own = INV ? (lane * M < TW && col < A.cols) : (lane * M >= K && col < A.cols);
     const R *src = in + part * A.ps;
     R *dst = out + part * A.ps;
-    using V = VecR<R, M>;
-    R prev[kK][2][NP][M];
+    R prev[KL][2][NP][M];
 #pragma unroll
-    for (int s = 0; s < kK; ++s)
+    for (int s = 0; s < KL; ++s)
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -229,140 +257,205 @@ __global__ __launch_bounds__(256, kConeWaves) void k_cone(const R *__restrict__ 
     };
     // rows the stream takes: ascending from r0 - kk + 1 (forward), descending from r1 - 1 + kk (inverse)
     int r = INV ? r1 - 1 + kk : r0 - kk + 1;
-    const int iters = ((r1 - r0) + (INV ? kk : kk - 1) + NR - 1) / NR;
-    request(r);
-#pragma unroll 1
-    for (int it = 0; it < iters; ++it) {
-        R x[NR][4][NP][M];
-#pragma unroll
-        for (int q = 0; q < NR; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int di = cone_di(TABLE, c), rq = INV ? r - q : r + q;
-                const bool rok = rq >= row_lo(t, di) && rq <= row_hi(t, di);
-#pragma unroll
-                for (int p = 0; p < NP; ++p)
-#pragma unroll
-                    for (int m = 0; m < M; ++m) x[q][c][p][m] = rok && ok[m] ? nx[q][c][p].v[m] : (R)0;
-            }
+    // (several stages: the same count in every wave of the block, and one group more per stage)
+    const int iters = ((NS > 1 ? A.seg_rows : r1 - r0) + (INV ? kk : kk - 1) + NR - 1) / NR;
+    if (NS == 1 || (active && stage == 0)) request(r);
+    r += (INV ? NR : -NR) * stage;
+    V *const mine = &hand[NS > 1 ? ((w / NS) * (NS - 1) + stage) * 2 * NR * 4 * NP * 64 : 0];  // what this stage hands on
+    const V *const from = stage > 0 ? mine - 2 * NR * 4 * NP * 64 : mine;                       // what the one before did
+    // every level with no test (a branch a level costs a fifth to a quarter of the time:
+    // 16384^2 H (x) H walk 37.1 against 29.5 ms) -- but in launches of fewer levels, with
+    // marks inside a stage, and for the rows the early levels alone work on
+    double nacc = 0.0;
+    const bool whole = kk == K && (!kScaled || sizeof(R) == 8 || inner_marks<KL>(A.marks) == 0);
+    auto group = [&](int g, auto some) {  // g: this stage's group
+        constexpr bool SOME = decltype(some)::value;
         const int rn = INV ? r - NR : r + NR;
-        request(rn);
-#pragma unroll
-        for (int s = 0; s < kK; ++s) {
-            // forward: coin, then the moves (the last move along I is the row it is
-            // stored to); inverse: the moves back, then the coin
-            auto coin = [&]() {
+        {
+            R x[NR][4][NP][M];
+            if (NS == 1 || stage == 0) {
 #pragma unroll
                 for (int q = 0; q < NR; ++q)
 #pragma unroll
-                    for (int m = 0; m < M; ++m) {
-                        R g[4][NP];
+                    for (int c = 0; c < 4; ++c) {
+                        const int di = cone_di(TABLE, c), rq = INV ? r - q : r + q;
+                        const bool rok = rq >= row_lo(t, di) && rq <= row_hi(t, di);
 #pragma unroll
-                        for (int c = 0; c < 4; ++c)
+                        for (int p = 0; p < NP; ++p)
 #pragma unroll
-                            for (int p = 0; p < NP; ++p) g[c][p] = x[q][c][p][m];
-                        site_coin<R, COIN, NP>(g, C);
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-#pragma unroll
-                            for (int p = 0; p < NP; ++p) x[q][c][p][m] = g[c][p];
+                            for (int m = 0; m < M; ++m) x[q][c][p][m] = rok && ok[m] ? nx[q][c][p].v[m] : (R)0;
                     }
-            };
-            auto move_j = [&]() {
+                request(rn);
+            } else {
 #pragma unroll
                 for (int q = 0; q < NR; ++q)
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        if (cone_dj(TABLE, c)) {
 #pragma unroll
-                            for (int p = 0; p < NP; ++p) {
-                                R(&v)[M] = x[q][c][p];
-                                if constexpr (INV) {
-                                    const R e = lane_shift<true>(v[0]);
+                        for (int p = 0; p < NP; ++p) {
+                            const V v = from[(((g & 1) * NR + q) * 4 * NP + c * NP + p) * 64 + lane];
 #pragma unroll
-                                    for (int m = 0; m + 1 < M; ++m) v[m] = v[m + 1];
-                                    v[M - 1] = e;
-                                } else {
-                                    const R e = lane_shift<false>(v[M - 1]);
-#pragma unroll
-                                    for (int m = M - 1; m > 0; --m) v[m] = v[m - 1];
-                                    v[0] = e;
-                                }
-                            }
+                            for (int m = 0; m < M; ++m) x[q][c][p][m] = v.v[m];
                         }
-            };
-            // the old rows, copied out before the level's outputs are made: the outputs
-            // can then be written where they were
-            R old[2][NP][M];
+            }
+            // levels of this stage that the group's last row works on
+            const int lim = min(kk, (g + 1) * NR) - stage * KL;
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+            for (int s = 0; s < KL; ++s) {
+                if (!SOME || s < lim) {
+                    // forward: coin, then the moves (the launch's last move along I is the
+                    // row it is stored to); inverse: the moves back, then the coin
+                    auto coin = [&]() {
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-#pragma unroll
-                    for (int m = 0; m < M; ++m)
-                        old[k][p][m] = INV || s < kK - 1 ? copy_out<INV>(prev[s][k][p][m]) : (R)0;
-            auto move_i = [&]() {
-                int k = 0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (cone_di(TABLE, c)) {
-#pragma unroll
-                        for (int p = 0; p < NP; ++p)
+                        for (int q = 0; q < NR; ++q)
 #pragma unroll
                             for (int m = 0; m < M; ++m) {
-                                prev[s][k][p][m] = x[NR - 1][c][p][m];
-                                asm volatile("" : "+v"(prev[s][k][p][m]));  // made here, not at the loop's end
-#pragma unroll
-                                for (int q = NR - 1; q > 0; --q) x[q][c][p][m] = x[q - 1][c][p][m];
-                                x[0][c][p][m] = old[k][p][m];
-                            }
-                        ++k;
-                    }
-            };
-            if (!PART || s < kk) {
-                if constexpr (INV) {
-                    move_i();
-                    move_j();
-                    coin();
-                } else {
-                    coin();
-                    if constexpr (PART && kScaled) {
-                        if (mark_at(A.marks, s)) {
-                            const R f = mark_scale<R>(A.marks, s);
-#pragma unroll
-                            for (int q = 0; q < NR; ++q)
+                                R v[4][NP];
 #pragma unroll
                                 for (int c = 0; c < 4; ++c)
 #pragma unroll
-                                    for (int p = 0; p < NP; ++p)
+                                    for (int p = 0; p < NP; ++p) v[c][p] = x[q][c][p][m];
+                                site_coin<R, COIN, NP>(v, C);
 #pragma unroll
-                                        for (int m = 0; m < M; ++m) x[q][c][p][m] *= f;
+                                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                                    for (int p = 0; p < NP; ++p) x[q][c][p][m] = v[c][p];
+                            }
+                    };
+                    auto move_j = [&]() {
+#pragma unroll
+                        for (int q = 0; q < NR; ++q)
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                if (cone_dj(TABLE, c)) {
+#pragma unroll
+                                    for (int p = 0; p < NP; ++p) {
+                                        R(&v)[M] = x[q][c][p];
+                                        if constexpr (INV) {
+                                            const R e = lane_shift<true>(v[0]);
+#pragma unroll
+                                            for (int m = 0; m + 1 < M; ++m) v[m] = v[m + 1];
+                                            v[M - 1] = e;
+                                        } else {
+                                            const R e = lane_shift<false>(v[M - 1]);
+#pragma unroll
+                                            for (int m = M - 1; m > 0; --m) v[m] = v[m - 1];
+                                            v[0] = e;
+                                        }
+                                    }
+                                }
+                    };
+                    // the old rows, copied out before the level's outputs are made: the
+                    // outputs can then be written where they were
+                    R old[2][NP][M];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+#pragma unroll
+                            for (int m = 0; m < M; ++m) old[k][p][m] = copy_out<INV>(prev[s][k][p][m]);
+                    auto move_i = [&]() {
+                        int k = 0;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (cone_di(TABLE, c)) {
+#pragma unroll
+                                for (int p = 0; p < NP; ++p)
+#pragma unroll
+                                    for (int m = 0; m < M; ++m) {
+                                        prev[s][k][p][m] = x[NR - 1][c][p][m];
+                                        asm volatile("" : "+v"(prev[s][k][p][m]));  // made here, not at the loop's end
+#pragma unroll
+                                        for (int q = NR - 1; q > 0; --q) x[q][c][p][m] = x[q - 1][c][p][m];
+                                        x[0][c][p][m] = old[k][p][m];
+                                    }
+                                ++k;
+                            }
+                    };
+                    if constexpr (INV) {
+                        move_i();
+                        move_j();
+                        coin();
+                    } else {
+                        const int gs = stage * KL + s;  // level of the launch
+                        coin();
+                        if constexpr (SOME && kScaled && sizeof(R) == 4) {
+                            if (s < KL - 1 && mark_at(A.marks, gs)) {
+                                const R f = mark_scale<R>(A.marks, gs);
+#pragma unroll
+                                for (int q = 0; q < NR; ++q)
+#pragma unroll
+                                    for (int c = 0; c < 4; ++c)
+#pragma unroll
+                                        for (int p = 0; p < NP; ++p)
+#pragma unroll
+                                            for (int m = 0; m < M; ++m) x[q][c][p][m] *= f;
+                            }
                         }
+                        move_j();
+                        if (SOME ? gs < kk - 1 : s < KL - 1 || stage < NS - 1) move_i();
                     }
-                    move_j();
-                    if (s < kK - 1 && (!PART || s < kk - 1)) move_i();
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (NS > 1 && stage < NS - 1) {
+                const int last = stage * KL + KL - 1;  // a mark there is applied here
+                const R f = kScaled && sizeof(R) == 4 && mark_at(A.marks, last) ? mark_scale<R>(A.marks, last) : (R)1;
+#pragma unroll
+                for (int q = 0; q < NR; ++q)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+#pragma unroll
+                        for (int p = 0; p < NP; ++p) {
+                            V v;
+#pragma unroll
+                            for (int m = 0; m < M; ++m) v.v[m] = kScaled && sizeof(R) == 4 ? x[q][c][p][m] * f : x[q][c][p][m];
+                            mine[(((g & 1) * NR + q) * 4 * NP + c * NP + p) * 64 + lane] = v;
+                        }
+            } else {
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    const int rq = INV ? r - q : r + q;
+                    if (rq >= r0 && rq < r1 && own) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+#pragma unroll
+                            for (int p = 0; p < NP; ++p) {
+                                V o;
+#pragma unroll
+                                for (int m = 0; m < M; ++m) o.v[m] = kScaled ? x[q][c][p][m] * (R)A.unscale : x[q][c][p][m];
+                                if (A.partial) {
+#pragma unroll
+                                    for (int m = 0; m < M; ++m)
+                                        if (col + m < A.cols) nacc = fmaR((double)o.v[m], (double)o.v[m], nacc);
+                                }
+                                *(V *)(dst + (2 * c + p) * A.ps + (int64_t)(INV ? rq : rq + cone_di(TABLE, c)) * A.ld + col) = o;
+                            }
+                    }
                 }
             }
-            // one level at a time: the scheduler would interleave several, whose old and
-            // new rows then need registers side by side
-            __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            const int rq = INV ? r - q : r + q;
-            if (rq >= r0 && rq < r1 && own) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        V o;
-#pragma unroll
-                        for (int m = 0; m < M; ++m) o.v[m] = kScaled ? x[q][c][p][m] * (R)A.unscale : x[q][c][p][m];
-                        *(V *)(dst + (2 * c + p) * A.ps + (int64_t)(INV ? rq : rq + cone_di(TABLE, c)) * A.ld + col) = o;
-                    }
-            }
-        }
-        r = rn;
+    };
+    // (two loops in sequence: both kinds of group in one would hold the registers of both)
+    const int total = iters + NS - 1, some = whole ? min(total, K / NR + NS - 2) : total;
+    int it = 0;
+#pragma unroll 1
+    for (; it < some; ++it) {
+        const int g = it - stage;
+        if (NS == 1 || (active && g >= 0 && g < iters)) group(g, std::true_type{});
+        if (NS > 1) __syncthreads();
+        r += INV ? -NR : NR;
+    }
+#pragma unroll 1
+    for (; it < total; ++it) {
+        const int g = it - stage;
+        if (NS == 1 || (active && g < iters)) group(g, std::false_type{});
+        if (NS > 1) __syncthreads();
+        r += INV ? -NR : NR;
+    }
+    if (A.partial && active && stage == NS - 1) {
+        nacc = wave_sum64(nacc);
+        if (lane == 0) A.partial[tile] = nacc;
     }
 }
 
@@ -479,6 +572,7 @@ __global__ __launch_bounds__(64 * kTW) void k_cone_tile(const R *__restrict__ in
         }
     }
     const bool own = INV ? (lane < 64 - kk && col < A.cols) : (lane >= kk && col < A.cols);
+    double nacc = 0.0;
 #pragma unroll
     for (int q = 0; q < RW; ++q) {
         const int r = INV ? first - q : first + q;
@@ -486,9 +580,22 @@ __global__ __launch_bounds__(64 * kTW) void k_cone_tile(const R *__restrict__ in
 #pragma unroll
             for (int c = 0; c < 4; ++c)
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-                    dst[(2 * c + p) * A.ps + (int64_t)(INV ? r : r + cone_di(TABLE, c)) * A.ld + col] =
-                        kScaled ? x[q][c][p] * (R)A.unscale : x[q][c][p];
+                for (int p = 0; p < NP; ++p) {
+                    const R v = kScaled ? x[q][c][p] * (R)A.unscale : x[q][c][p];
+                    dst[(2 * c + p) * A.ps + (int64_t)(INV ? r : r + cone_di(TABLE, c)) * A.ld + col] = v;
+                    nacc = fmaR((double)v, (double)v, nacc);
+                }
+        }
+    }
+    if (A.partial) {  // uniform over the launch
+        __shared__ double ws[kTW];
+        nacc = wave_sum64(nacc);
+        if (lane == 0) ws[wave] = nacc;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double n = 0.0;
+            for (int i = 0; i < kTW; ++i) n += ws[i];
+            A.partial[blockIdx.x] = n;
         }
     }
 }
@@ -577,35 +684,45 @@ __device__ __forceinline__ double point_prob(const R *__restrict__ a, const Cone
 // P over the whole lattice.  A block writes 64 x 64 sites.  With the axis-aligned
 // tables a lattice row runs along a diagonal of the square, so the block takes
 // its points in the square's order (coalesced loads) into an LDS tile and writes
-// the tile's rows; with the diagonal table rows are rows.
+// the tile's rows; with the diagonal table rows are rows.  A tile off the cone
+// (most of them, on a large torus) writes its zeros at once.  Bound by the writes.
 constexpr int kPT = 64, kPPitch = kPT + 2;  // pitch: a diagonal's points fall on different banks
+struct alignas(8) Pair64 {
+    double a, b;
+};
 template <typename R, int TABLE>
-__global__ __launch_bounds__(256) void k_cone_prob(const R *__restrict__ a, ConeView V, double *__restrict__ P) {
+__global__ __launch_bounds__(256) void k_cone_prob(const R *__restrict__ a, ConeView V, double *__restrict__ P, int skew) {
     __shared__ double s[kPT * kPPitch];
-    // the tile's first offset: offsets run over (-L/2, L/2]
-    const int bx = (int)blockIdx.x * kPT - (V.g.Lx - 1) / 2, by = (int)blockIdx.y * kPT - (V.g.Ly - 1) / 2;
-    const int t = V.t, tid = threadIdx.x;
-    const int nx = min(kPT, V.g.Lx / 2 - bx + 1), ny = min(kPT, V.g.Ly / 2 - by + 1);  // tile inside the lattice
-    for (int i = tid; i < kPT * kPPitch; i += 256) s[i] = 0.0;
-    __syncthreads();
-    // points whose sites may lie in the tile (floor halves)
-    const int Ia = (TABLE == TABLE_DIAG ? by + t : bx + by + t) >> 1;
-    const int Ja = (TABLE == TABLE_DIAG ? bx + t : bx - by - (kPT - 1) + t) >> 1;
-    constexpr int kN = TABLE == TABLE_DIAG ? kPT / 2 + 1 : kPT + 1;
-    for (int k = tid; k < kN * kN; k += 256) {
-        const int I = Ia + k / kN, J = Ja + k % kN;
-        if (I < 0 || I > t || J < 0 || J > t) continue;
-        const int dx = TABLE == TABLE_DIAG ? 2 * J - t : I + J - t, dy = TABLE == TABLE_DIAG ? 2 * I - t : I - J;
-        const int lx = dx - bx, ly = dy - by;
-        if (lx < 0 || lx >= nx || ly < 0 || ly >= ny) continue;
-        s[ly * kPPitch + lx] = point_prob<R, TABLE>(a, V, I, J);
+    // the tile's first offset: offsets run over (-L/2, L/2]; the first column of tiles
+    // starts skew sites early, on a 128-byte line of P
+    const int Lx = V.g.Lx, Ly = V.g.Ly, t = V.t, tid = threadIdx.x;
+    const int bx = (int)blockIdx.x * kPT - (Lx - 1) / 2 - skew, by = (int)blockIdx.y * kPT - (Ly - 1) / 2;
+    const int lx0 = blockIdx.x == 0 ? skew : 0;                                  // tile inside the lattice
+    const int nx = min(kPT, Lx / 2 - bx + 1), ny = min(kPT, Ly / 2 - by + 1);
+    // distance of the tile from the start site along each axis
+    const int gx = max(0, max(bx, -(bx + kPT - 1))), gy = max(0, max(by, -(by + kPT - 1)));
+    const bool empty = TABLE == TABLE_DIAG ? gx > t || gy > t : gx + gy > t;  // uniform over the block
+    if (!empty) {
+        for (int i = tid; i < kPT * kPPitch; i += 256) s[i] = 0.0;
+        __syncthreads();
+        // points whose sites may lie in the tile (floor halves)
+        const int Ia = (TABLE == TABLE_DIAG ? by + t : bx + by + t) >> 1;
+        const int Ja = (TABLE == TABLE_DIAG ? bx + t : bx - by - (kPT - 1) + t) >> 1;
+        constexpr int kN = TABLE == TABLE_DIAG ? kPT / 2 + 1 : kPT + 1;
+        for (int k = tid; k < kN * kN; k += 256) {
+            const int I = Ia + k / kN, J = Ja + k % kN;
+            if (I < 0 || I > t || J < 0 || J > t) continue;
+            const int dx = TABLE == TABLE_DIAG ? 2 * J - t : I + J - t, dy = TABLE == TABLE_DIAG ? 2 * I - t : I - J;
+            const int lx = dx - bx, ly = dy - by;
+            if (lx < 0 || lx >= nx || ly < 0 || ly >= ny) continue;
+            s[ly * kPPitch + lx] = point_prob<R, TABLE>(a, V, I, J);
+        }
+        __syncthreads();
     }
-    __syncthreads();
     // t = L / 2: the points at offset -t are the sites at +t
-    const bool ax = 2 * t == V.g.Lx && t > 0, ay = 2 * t == V.g.Ly && t > 0;
-    for (int k = tid; k < kPT * kPT; k += 256) {
-        const int lx = k % kPT, ly = k / kPT;
-        if (lx >= nx || ly >= ny) continue;
+    const bool ax = 2 * t == Lx && t > 0, ay = 2 * t == Ly && t > 0;
+    auto at = [&](int lx, int ly) -> double {
+        if (empty) return 0.0;
         const int dx = bx + lx, dy = by + ly;
         double p = s[ly * kPPitch + lx];
         if ((ax && dx == t) || (ay && dy == t)) {
@@ -614,10 +731,21 @@ __global__ __launch_bounds__(256) void k_cone_prob(const R *__restrict__ a, Cone
             if (ay && dy == t && cone_point<TABLE>(t, dx, -t, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
             if (ax && dx == t && ay && dy == t && cone_point<TABLE>(t, -t, -t, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
         }
-        int x = V.x0 + dx, y = V.y0 + dy;
-        x = x < 0 ? x + V.g.Lx : (x >= V.g.Lx ? x - V.g.Lx : x);
-        y = y < 0 ? y + V.g.Ly : (y >= V.g.Ly ? y - V.g.Ly : y);
-        P[(int64_t)y * V.g.Lx + x] = p;
+        return p;
+    };
+    for (int k = tid; k < kPT * kPT / 2; k += 256) {
+        const int lx = 2 * (k % (kPT / 2)), ly = k / (kPT / 2);
+        if (ly >= ny || lx >= nx || lx + 1 < lx0) continue;
+        int x = V.x0 + bx + lx, y = V.y0 + by + ly;
+        x = x < 0 ? x + Lx : (x >= Lx ? x - Lx : x);
+        y = y < 0 ? y + Ly : (y >= Ly ? y - Ly : y);
+        double *row = P + (int64_t)y * Lx;
+        if (lx >= lx0 && lx + 1 < nx && x + 1 < Lx) {
+            *(Pair64 *)(row + x) = Pair64{at(lx, ly), at(lx + 1, ly)};
+        } else {
+            if (lx >= lx0) row[x] = at(lx, ly);
+            if (lx + 1 < nx) row[x + 1 < Lx ? x + 1 : 0] = at(lx + 1, ly);
+        }
     }
 }
 
@@ -628,8 +756,7 @@ __global__ __launch_bounds__(256) void k_cone_norm(const R *__restrict__ a, Cone
     double acc = 0.0;
     for (int I = blockIdx.x; I <= V.t; I += gridDim.x)
         for (int J = threadIdx.x; J <= V.t; J += 256) acc += point_prob<R, TABLE>(a, V, I, J);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    acc = wave_sum64(acc);
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) partial[blockIdx.x] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
@@ -672,12 +799,36 @@ int cone_tiles(int rows, int cols, int kk, bool inv, int RW, int parts) {
     return ((rows + TR - 1) / TR) * ((cols + TC - 1) / TC) * parts;
 }
 
-// M, NR: columns per lane and rows per group of k_cone; the tile kernel takes 2
-// rows per wave (real lanes) or 1
+template <typename K, typename R>
+void cone_go(K kernel, unsigned blocks, unsigned threads, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const void *in,
+             void *out, const ConeArgs &A, const CoinF64 &C) {
+    if (e0) hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, s, e0, e1, 0u, (const R *)in, (R *)out, A, to_coin<R>(C));
+    else hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, s, (const R *)in, (R *)out, A, to_coin<R>(C));
+}
+
+// strips, segments and blocks of a launch of k_cone<R, KL, NS, M, ...>
+template <typename R, int KL, int NS, int M, bool CPLX> unsigned cone_shape(ConeArgs &A, int waves_per_simd, LaunchInfo *info) {
+    constexpr int TW = 64 * M - KL * NS;
+    A.nstrips = (A.cols + TW - 1) / TW;
+    // segments that give every SIMD its waves, but not so short that the kk - 1 rows
+    // each reads before its first cost more than they save
+    const long per = (long)A.nstrips * (CPLX ? 1 : 2);
+    const long segs = std::max(1L, 4L * cone_cus() * waves_per_simd / NS / per);
+    A.seg_rows = std::max((int)((A.rows + segs - 1) / segs), kConeMinRows);
+    A.nseg = (A.rows + A.seg_rows - 1) / A.seg_rows;
+    const long tiles = per * A.nseg;
+    if (info) {
+        info->bytes_read = (double)tiles * 64 * M * (CPLX ? 8 : 4) * sizeof(R) * (A.seg_rows + A.kk);
+        info->bytes_written = 8.0 * sizeof(R) * A.rows * A.cols;
+    }
+    return (unsigned)((tiles * NS + 3) / 4);
+}
+
+// M, NR: columns per lane and rows per group of the one-stage kernel; the tile
+// kernel takes 2 rows per wave (real lanes) or 1
 template <typename R, int M, int NR, int TABLE, int COIN, bool CPLX, bool INV>
-void cone_launch(const void *in, void *out, const Cone &cn, int kk, uint32_t marks, const CoinF64 &C, hipStream_t s, LaunchInfo *info,
-                 hipEvent_t ev0, hipEvent_t ev1) {
-    constexpr int TW = 64 * M - kK;
+void cone_launch(const void *in, void *out, const Cone &cn, int kk, uint32_t marks, const CoinF64 &C, hipStream_t s,
+                 LaunchInfo *info, Scratch *norm, hipEvent_t ev0, hipEvent_t ev1) {
     constexpr int parts = CPLX ? 1 : 2;
     constexpr int RW = CPLX ? 1 : 2;
     ConeArgs A;
@@ -688,79 +839,66 @@ void cone_launch(const void *in, void *out, const Cone &cn, int kk, uint32_t mar
     const int t1 = INV ? cn.t - kk : cn.t + kk;
     A.rows = INV ? t1 + 1 : t1;
     A.cols = t1 + 1;
-    A.marks = marks & ((1u << (kk - 1)) - 1u);
-    A.unscale = 1.0 / (double)(1u << (A.marks ? kk - (32 - __builtin_clz(A.marks)) : kk));
-    unsigned blocks;
+    A.partial = nullptr;
+    auto sums = [&](long n) {  // the launch's tiles or blocks, one partial sum each
+        if (norm && n <= kRedBlocks) {
+            A.partial = norm->partial;
+            info->norm_parts = (int)n;
+        }
+    };
+    A.marks = marks & (uint32_t)((1ull << (kk - 1)) - 1u);
+    A.unscale = 1.0 / (double)(1ull << (A.marks ? kk - (32 - __builtin_clz(A.marks)) : kk));
     // (a tile deeper than kTileDepth would have no rows left)
     if (kk <= kTileDepth<CPLX> && cone_tiles(A.rows, A.cols, kk, INV, RW, parts) <= kConeTilesPerCu * cone_cus()) {
         A.nstrips = (A.cols + 63 - kk) / (64 - kk);
         A.seg_rows = kTW * RW - (INV ? kk : kk - 1);
         A.nseg = (A.rows + A.seg_rows - 1) / A.seg_rows;
-        blocks = (unsigned)(A.nstrips * A.nseg * parts);
+        const unsigned blocks = (unsigned)(A.nstrips * A.nseg * parts);
         if (info) {
             info->bytes_read = (double)blocks * kTW * RW * 64 * (CPLX ? 8 : 4) * sizeof(R);
             info->bytes_written = 8.0 * sizeof(R) * A.rows * A.cols;
         }
-        if (ev0)
-            hipExtLaunchKernelGGL((k_cone_tile<R, RW, TABLE, COIN, CPLX, INV>), dim3(blocks), dim3(64 * kTW), 0, s, ev0,
-                                  ev1, 0u, (const R *)in, (R *)out, A, to_coin<R>(C));
-        else
-            hipLaunchKernelGGL((k_cone_tile<R, RW, TABLE, COIN, CPLX, INV>), dim3(blocks), dim3(64 * kTW), 0, s,
-                               (const R *)in, (R *)out, A, to_coin<R>(C));
+        sums(blocks);
+        auto *k = k_cone_tile<R, RW, TABLE, COIN, CPLX, INV>;
+        cone_go<decltype(k), R>(k, blocks, 64 * kTW, s, ev0, ev1, in, out, A, C);
         return;
     }
-    A.nstrips = (A.cols + TW - 1) / TW;
-    // segments: enough waves to fill the chip twice over per SIMD, but not so short
-    // that the kk - 1 rows each reads before its first cost more than they save
-    const long target = 4L * cone_cus() * kConeWaves;
-    const long per = (long)A.nstrips * parts;
-    long segs = std::max(1L, target / per);
-    A.seg_rows = std::max((int)((A.rows + segs - 1) / segs), kConeMinRows);
-    A.nseg = (A.rows + A.seg_rows - 1) / A.seg_rows;
-    const long waves = per * A.nseg;
-    blocks = (unsigned)((waves + 3) / 4);
-    if (info) {
-        info->bytes_read = (double)waves * 64 * M * (CPLX ? 8 : 4) * sizeof(R) * (A.seg_rows + kk);
-        info->bytes_written = 8.0 * sizeof(R) * A.rows * A.cols;
+    if constexpr (!CPLX && !INV) {
+        if (kk > kK) {
+            const unsigned blocks = cone_shape<R, kDeepKL, kDeepNS, kDeepM<R>, CPLX>(A, 2, info);
+            sums((long)A.nstrips * A.nseg * parts);
+            auto *k = k_cone<R, kDeepKL, kDeepNS, kDeepM<R>, kDeepNR, TABLE, COIN, CPLX, INV>;
+            cone_go<decltype(k), R>(k, blocks, 256, s, ev0, ev1, in, out, A, C);
+            return;
+        }
     }
-#define QW_CONE_LAUNCH(PART)                                                                                            \
-    do {                                                                                                                \
-        if (ev0)                                                                                                        \
-            hipExtLaunchKernelGGL((k_cone<R, M, NR, TABLE, COIN, CPLX, INV, PART>), dim3(blocks), dim3(256), 0, s, ev0, \
-                                  ev1, 0u, (const R *)in, (R *)out, A, to_coin<R>(C), 1);                               \
-        else                                                                                                            \
-            hipLaunchKernelGGL((k_cone<R, M, NR, TABLE, COIN, CPLX, INV, PART>), dim3(blocks), dim3(256), 0, s,         \
-                               (const R *)in, (R *)out, A, to_coin<R>(C), 1);                                           \
-    } while (0)
-    if constexpr (INV) {
-        QW_CONE_LAUNCH(true);
-    } else {
-        if (kk == kK && A.marks == 0) QW_CONE_LAUNCH(false);
-        else QW_CONE_LAUNCH(true);
-    }
-#undef QW_CONE_LAUNCH
+    const unsigned blocks = cone_shape<R, kK, 1, M, CPLX>(A, kConeWaves, info);
+    sums((long)A.nstrips * A.nseg * parts);
+    auto *k = k_cone<R, kK, 1, M, NR, TABLE, COIN, CPLX, INV>;
+    cone_go<decltype(k), R>(k, blocks, 256, s, ev0, ev1, in, out, A, C);
 }
 
 template <typename R, int TABLE>
-hipError_t cone_table(int coin_impl, bool inverse, const void *in, void *out, const Cone &cn, int kk, uint32_t marks, const CoinF64 &C,
-                      hipStream_t s, LaunchInfo *info, hipEvent_t e0, hipEvent_t e1) {
+hipError_t cone_table(int coin_impl, bool inverse, const void *in, void *out, const Cone &cn, int kk, uint32_t marks,
+                      const CoinF64 &C, hipStream_t s, LaunchInfo *info, Scratch *norm, hipEvent_t e0, hipEvent_t e1) {
     constexpr int M = sizeof(R) == 8 ? 2 : 4;   // real lanes
     constexpr int MC = sizeof(R) == 8 ? 1 : 2;  // complex lanes
     bool real = true;
     for (int i = 0; i < 16; ++i) real = real && C.im[i] == 0.0;
+#define QW_CONE_ARGS in, out, cn, kk, marks, C, s, info, norm, e0, e1
     if (inverse) {
-        if (real) cone_launch<R, M, 2, TABLE, COIN_DENSE, false, true>(in, out, cn, kk, marks, C, s, info, e0, e1);
-        else cone_launch<R, MC, 1, TABLE, COIN_DENSE, true, true>(in, out, cn, kk, marks, C, s, info, e0, e1);
+        if (real) cone_launch<R, M, 2, TABLE, COIN_DENSE, false, true>(QW_CONE_ARGS);
+        else cone_launch<R, MC, 1, TABLE, COIN_DENSE, true, true>(QW_CONE_ARGS);
     } else if (coin_impl == COIN_GROVER4) {
-        cone_launch<R, M, 2, TABLE, COIN_GROVER4, false, false>(in, out, cn, kk, marks, C, s, info, e0, e1);
+        cone_launch<R, M, 2, TABLE, COIN_GROVER4, false, false>(QW_CONE_ARGS);
     } else if (coin_impl == COIN_HH4) {
-        cone_launch<R, M, 2, TABLE, COIN_HH4, false, false>(in, out, cn, kk, marks, C, s, info, e0, e1);
+        cone_launch<R, M, 2, TABLE, COIN_HH4, false, false>(QW_CONE_ARGS);
     } else if (sizeof(R) == 8 && cn.fourier) {
-        if constexpr (sizeof(R) == 8)
-            cone_launch<R, MC, 1, TABLE, kCoinFourier4, true, false>(in, out, cn, kk, marks, C, s, info, e0, e1);
+        if constexpr (sizeof(R) == 8) cone_launch<R, MC, 1, TABLE, kCoinFourier4, true, false>(QW_CONE_ARGS);
     } else {
-        cone_launch<R, MC, 1, TABLE, COIN_DENSE, true, false>(in, out, cn, kk, marks, C, s, info, e0, e1);
+        cone_launch<R, MC, 1, TABLE, COIN_DENSE, true, false>(QW_CONE_ARGS);
     }
+#undef QW_CONE_ARGS
     return hipGetLastError();
 }
 
@@ -779,17 +917,19 @@ hipError_t cone_table(int coin_impl, bool inverse, const void *in, void *out, co
 
 }  // namespace
 
-int cone_max_depth() { return kK; }
+int cone_max_depth() { return 2 * kK; }
 
 int cone_depth(int coin_impl, bool inverse, const Cone &c, const CoinF64 &C, int64_t left, int max_depth) {
-    const int kk = (int)std::min<int64_t>(left, std::min(max_depth, kK));
+    int kk = (int)std::min<int64_t>(left, std::min(max_depth, 2 * kK));
     bool real = coin_impl != COIN_DENSE || inverse;
     for (int i = 0; i < 16; ++i) real = real && C.im[i] == 0.0;
     const int kt = real ? kTileDepth<false> : kTileDepth<true>;
     if (kk <= kt) return kk;
     const int t1 = inverse ? c.t - kt : c.t + kt;
     const int tiles = cone_tiles(inverse ? t1 + 1 : t1, t1 + 1, kt, inverse, real ? 2 : 1, real ? 2 : 1);
-    return tiles <= kConeTilesPerCu * cone_cus() ? kt : kk;
+    if (tiles <= kConeTilesPerCu * cone_cus()) return kt;
+    if (kk > kK && (inverse || !real || c.t < kDeepSide)) kk = kK;
+    return kk;
 }
 
 bool cone_fits(const Geom &g, int table, size_t state_bytes, int prec, Cone *c) {
@@ -815,9 +955,9 @@ hipError_t launch_cone_place(int prec, void *state, const Cone &c, const double 
 
 hipError_t launch_cone_steps(int prec, int coin_impl, int table, bool inverse, const void *in, void *out, const Cone &c,
                              int kk, uint32_t marks, const CoinF64 &C, hipStream_t s, LaunchInfo *info,
-                             hipEvent_t ev_start, hipEvent_t ev_stop) {
-    if (kk < 1 || kk > kK || (inverse ? kk > c.t : c.t + kk > c.tmax)) return hipErrorInvalidValue;
-#define QW_CALL(R, TAB) return cone_table<R, TAB>(coin_impl, inverse, in, out, c, kk, marks, C, s, info, ev_start, ev_stop)
+                             Scratch *norm, hipEvent_t ev_start, hipEvent_t ev_stop) {
+    if (kk < 1 || kk > 2 * kK || (kk > kK && inverse) || (inverse ? kk > c.t : c.t + kk > c.tmax)) return hipErrorInvalidValue;
+#define QW_CALL(R, TAB) return cone_table<R, TAB>(coin_impl, inverse, in, out, c, kk, marks, C, s, info, norm, ev_start, ev_stop)
     QW_CONE_DISPATCH(prec, table, QW_CALL);
 #undef QW_CALL
     return hipErrorInvalidValue;
@@ -825,8 +965,11 @@ hipError_t launch_cone_steps(int prec, int coin_impl, int table, bool inverse, c
 
 hipError_t launch_cone_prob(int prec, int table, const void *state, const Cone &c, const Geom &g, double *P, hipStream_t s) {
     const ConeView V = cone_view(c, g);
-    const dim3 grid((g.Lx + kPT - 1) / kPT, (g.Ly + kPT - 1) / kPT);
-#define QW_CALL(R, TAB) hipLaunchKernelGGL((k_cone_prob<R, TAB>), grid, dim3(256), 0, s, (const R *)state, V, P)
+    // the lattice column of the first offset, down to a line of 16
+    int first = (int)(((int64_t)c.x0 - (g.Lx - 1) / 2 + g.Lx) % g.Lx);
+    const int skew = first % 16;
+    const dim3 grid((g.Lx + skew + kPT - 1) / kPT, (g.Ly + kPT - 1) / kPT);
+#define QW_CALL(R, TAB) hipLaunchKernelGGL((k_cone_prob<R, TAB>), grid, dim3(256), 0, s, (const R *)state, V, P, skew)
     QW_CONE_DISPATCH(prec, table, QW_CALL);
 #undef QW_CALL
     return hipGetLastError();

@@ -45,6 +45,7 @@ struct Scratch {
 // HBM bytes a launch moves by construction (state reads incl. halo, writes)
 struct LaunchInfo {
     double bytes_read = 0.0, bytes_written = 0.0;
+    int norm_parts = 0;  // partial sums of the norm the launch left in the scratch area (0: none)
 };
 
 // ---- launchers (qw_kernels.hip); all return a hipError_t ----
@@ -173,14 +174,16 @@ int cone_max_depth();  // most steps of one launch
 int cone_depth(int coin_impl, bool inverse, const Cone &c, const CoinF64 &C, int64_t left, int max_depth);
 // psi_0 into the square of t = 0
 hipError_t launch_cone_place(int prec, void *state, const Cone &c, const double *psi0, hipStream_t s);
-// kk steps (of U, or U^-1 with C = C^dagger) from the state of time c.t: kk <=
-// cone_max_depth(), c.t + kk <= c.tmax, or kk <= c.t for the inverse.  marks: bit s
+// kk steps (of U, or U^-1 with C = C^dagger) from the state of time c.t: kk as
+// cone_depth gave it, c.t + kk <= c.tmax, or kk <= c.t for the inverse.  marks: bit s
 // set where the kernels of the whole lattice would store the state after step s + 1
 // (the coins that keep a factor 2 per step out multiply it back there, which
-// rounds subnormal values); the launch's end is always one
+// rounds subnormal values); the launch's end is always one.  norm (may be null):
+// the launch also sums the squares it stores, where its tiles fit the partial
+// sums there (info->norm_parts of them)
 hipError_t launch_cone_steps(int prec, int coin_impl, int table, bool inverse, const void *in, void *out, const Cone &c,
-                             int kk, uint32_t marks, const CoinF64 &C, hipStream_t s, LaunchInfo *info, hipEvent_t ev_start,
-                             hipEvent_t ev_stop);
+                             int kk, uint32_t marks, const CoinF64 &C, hipStream_t s, LaunchInfo *info, Scratch *norm,
+                             hipEvent_t ev_start, hipEvent_t ev_stop);
 // P(x) over the whole lattice
 hipError_t launch_cone_prob(int prec, int table, const void *state, const Cone &c, const Geom &g, double *P, hipStream_t s);
 // the fp64 norm into scratch->norm; the conditional rescale, as launch_renorm
