@@ -627,21 +627,62 @@ __global__ void k_features(int64_t n, const int64_t *__restrict__ N, const int64
 }
 
 // network inputs of n walks, padded with zero rows to npad: bf16 features and
-// the step counts clamped to the head's site table
-__global__ void k_net_inputs(int64_t n, int64_t npad, const int64_t *__restrict__ N, const int64_t *__restrict__ T,
-                             const double *__restrict__ ang, const double *__restrict__ psi0, bf16_t *__restrict__ Xb,
-                             int32_t *__restrict__ T32) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < npad; i += (int64_t)gridDim.x * blockDim.x) {
-        float x[kF];
-        if (i < n) {
-            feature_row(i, N, T, ang, psi0, x);
-            T32[i] = (int32_t)min(max(T[i], (int64_t)0), (int64_t)(kMaxSites - 1));
-        } else {
-            for (int k = 0; k < kF; ++k) x[k] = 0.0f;
-            T32[i] = 0;
+// the step counts clamped to the head's site table.  Four lanes per walk, each with
+// its share of feature_row's fp64 functions (the same expressions): the time is their
+// latency in series, which one thread per walk paid whole (60001 walks: 55 us).
+__global__ __launch_bounds__(64) void k_net_inputs(int64_t n, int64_t npad, const int64_t *__restrict__ N,
+                                                   const int64_t *__restrict__ T, const double *__restrict__ ang,
+                                                   const double *__restrict__ psi0, bf16_t *__restrict__ Xb,
+                                                   int32_t *__restrict__ T32) {
+    const int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 2);
+    const int q = threadIdx.x & 3;
+    if (i >= npad) return;
+    float x[8];  // lane q holds features 2 q, 2 q + 1 (angles); 6 .. 8 (lane 3); 9 (lane 0); 10, 11 (lane 2)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = 0.0f;
+    if (i < n) {
+        const double ar = psi0[4 * i], ai = psi0[4 * i + 1], br = psi0[4 * i + 2], bi = psi0[4 * i + 3];
+        const double aa = sqrt(ar * ar + ai * ai);
+        // the two arguments, each in one lane of a pair
+        const double sy = q & 1 ? ai : bi, sx = q & 1 ? ar : br;
+        const bool has = q & 1 ? aa > 0.0 : br != 0.0 || bi != 0.0;
+        const double arg = has ? atan2(sy, sx) : 0.0, other = __shfl_xor(arg, 1);
+        const double arga = q & 1 ? arg : other, argb = q & 1 ? other : arg;
+        // lane 3 takes arg a, the others their angle; then lane 2 the relative phase
+        const double th = q == 3 ? arga : ang[3 * i + q];
+        const double s = sin(th), c = cos(th);
+        x[0] = (float)s;
+        x[1] = (float)c;
+        if (q == 3) {
+            x[2] = (float)aa;
+            x[3] = (float)(br * c + bi * s);  // b e^{-i arg a}
+            x[4] = (float)(bi * c - br * s);
         }
-        for (int k = 0; k < kF; ++k) Xb[i * kF + k] = f2bf(x[k]);
+        if (q == 0) x[2] = (float)((double)T[i] / (double)N[i]);
+        if (q == 2) {
+            const double dl = argb - arga + ang[3 * i + 2] - ang[3 * i + 1];
+            x[2] = (float)cos(dl);
+            x[3] = (float)sin(dl);
+        }
+        if (q == 0) T32[i] = (int32_t)min(max(T[i], (int64_t)0), (int64_t)(kMaxSites - 1));
+    } else if (q == 0) {
+        T32[i] = 0;
     }
+    bf16_t *row = Xb + i * kF;
+    if (q < 3) {
+        row[2 * q] = f2bf(x[0]);
+        row[2 * q + 1] = f2bf(x[1]);
+    }
+    if (q == 3) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) row[6 + k] = f2bf(x[2 + k]);
+    }
+    if (q == 0) row[9] = f2bf(x[2]);
+    if (q == 2) {
+        row[10] = f2bf(x[2]);
+        row[11] = f2bf(x[3]);
+    }
+    for (int k = 12 + 5 * q; k < 17 + 5 * q; ++k) row[k] = f2bf(0.0f);
 }
 
 // the same for features given as fp32 rows (steps already int32)
@@ -739,7 +780,16 @@ double unif(uint64_t &s) { return (splitmix(s) >> 11) * (1.0 / 9007199254740992.
 
 }  // namespace
 
+struct WorkBuf {
+    void *p = nullptr;
+    size_t bytes = 0;
+};
+
 struct qw_surr {
+    // surr_predict and surr_forward: network inputs and output; walk parameters, re-check
+    // indices, plain and gathered bins, distances
+    WorkBuf w_xb, w_t32, w_out, w_n, w_t, w_a, w_p, w_idx, w_plain, w_net, w_tv;
+    hipEvent_t ev[2] = {nullptr, nullptr};
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int bmax = 16384;  // rows per network pass (training batches, forward chunks)
@@ -766,6 +816,11 @@ void free_surr(qw_surr *s) {
     void *bufs[] = {s->p, s->m, s->v, s->g, s->pb, s->W2T, s->W3T, s->W4T, s->xb, s->h1, s->h2, s->h3,
                     s->z4, s->q, s->yb, s->dl, s->lrow, s->part, s->dz, s->dzb, s->dzb2, s->dzT, s->hT, s->idx, s->tb};
     for (void *b : bufs) (void)hipFree(b);
+    for (WorkBuf *w : {&s->w_xb, &s->w_t32, &s->w_out, &s->w_n, &s->w_t, &s->w_a, &s->w_p, &s->w_idx, &s->w_plain, &s->w_net,
+                       &s->w_tv})
+        (void)hipFree(w->p);
+    for (hipEvent_t e : s->ev)
+        if (e) (void)hipEventDestroy(e);
     if (s->own_stream) (void)hipStreamDestroy(s->stream);
     delete s;
 }
@@ -851,8 +906,9 @@ hipError_t refresh_weights(qw_surr *s) {
 // forward of B rows already in s->xb; y (device, B x 512) optional -> dl, lrow
 // network forward on B rows (a multiple of 128): inputs xin / tin (default:
 // the handle's batch buffers), output p into qout (default: s->q)
+// (rows >= 0: that many of the B rows go through the head and into qout)
 hipError_t forward(qw_surr *s, int B, int Bscale, const float *y, const bf16_t *xin = nullptr,
-                   const int32_t *tin = nullptr, float *qout = nullptr) {
+                   const int32_t *tin = nullptr, float *qout = nullptr, int rows = -1) {
     hipStream_t st = s->stream;
     if (!xin) xin = s->xb;
     if (!tin) tin = s->tb;
@@ -871,39 +927,38 @@ hipError_t forward(qw_surr *s, int B, int Bscale, const float *y, const bf16_t *
                            (const float *)(s->p + L.cw), (const float *)(s->p + L.cb), tin, w < 1 ? 1 : w, qout, y,
                            s->dl, s->lrow, Bscale);
     else
-        hipLaunchKernelGGL(k_head_fwd<false>, dim3(B), dim3(256), 0, st, (const float *)s->z4,
+        hipLaunchKernelGGL(k_head_fwd<false>, dim3(rows >= 0 ? rows : B), dim3(256), 0, st, (const float *)s->z4,
                            (const float *)(s->p + L.cw), (const float *)(s->p + L.cb), tin, w < 1 ? 1 : w, qout,
                            nullptr, nullptr, nullptr, Bscale);
     return hipGetLastError();
 }
 
 // network output of n rows whose inputs are on the device (Xb: npad x 32
-// bf16, T32: npad, npad = n rounded up to 128) into dout (device, npad x 512);
+// bf16, T32: npad, npad = n rounded up to 128) into dout (device, n x 512);
 // no synchronisation
-hipError_t forward_rows(qw_surr *s, int64_t npad, const bf16_t *Xb, const int32_t *T32, float *dout) {
+hipError_t forward_rows(qw_surr *s, int64_t n, int64_t npad, const bf16_t *Xb, const int32_t *T32, float *dout) {
     for (int64_t r0 = 0; r0 < npad; r0 += s->bmax) {
         const int bp = (int)std::min<int64_t>(s->bmax, npad - r0);
-        hipError_t e = forward(s, bp, bp, nullptr, Xb + r0 * kF, T32 + r0, dout + r0 * kBins);
+        hipError_t e = forward(s, bp, bp, nullptr, Xb + r0 * kF, T32 + r0, dout + r0 * kBins,
+                               (int)std::min<int64_t>(bp, n - r0));
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-// device scratch of one network-only pass over n walks
-struct NetBufs {
-    int64_t npad = 0;
-    bf16_t *xb = nullptr;
-    int32_t *t32 = nullptr;
-    float *out = nullptr;
-    ~NetBufs() { (void)hipFree(xb); (void)hipFree(t32); (void)hipFree(out); }
-    hipError_t alloc(int64_t n) {
-        npad = (n + 127) / 128 * 128;
-        hipError_t e = hipMalloc((void **)&xb, sizeof(bf16_t) * npad * kF);
-        if (e == hipSuccess) e = hipMalloc((void **)&t32, sizeof(int32_t) * npad);
-        if (e == hipSuccess) e = hipMalloc((void **)&out, sizeof(float) * npad * kBins);
-        return e;
-    }
-};
+// Device memory that a handle's predictions reuse, grown to the largest call's need
+// and released with the handle (allocating it in each call cost as much as the
+// network: 60001 walks 2.06 -> 1.5 ms with the overlap of surr_predict).
+hipError_t room(WorkBuf &w, size_t bytes) {
+    if (w.bytes >= bytes) return hipSuccess;
+    (void)hipFree(w.p);
+    w.p = nullptr;
+    w.bytes = 0;
+    const hipError_t e = hipMalloc(&w.p, bytes);
+    if (e == hipSuccess) w.bytes = bytes;
+    else (void)hipGetLastError();
+    return e;
+}
 
 // backward of the batch of the last forward (with targets): gradients into s->g
 // loss_sum (device, optional): receives the sum of the per-sample losses the
@@ -1122,21 +1177,26 @@ int surr_features(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, co
 
 int surr_forward(qw_surr_t s, int64_t n, const float *X, const int32_t *T, float *out) {
     if (!s || !X || !T || !out || n < 1) return sfail(QW_EINVAL, "bad arguments");
-    NetBufs nb;
+    const int64_t npad = (n + 127) / 128 * 128;
     float *dX = nullptr;
     int32_t *dT = nullptr;
-    hipError_t e = nb.alloc(n);
+    hipError_t e = room(s->w_xb, sizeof(bf16_t) * npad * kF);
+    if (e == hipSuccess) e = room(s->w_t32, sizeof(int32_t) * npad);
+    if (e == hipSuccess) e = room(s->w_out, sizeof(float) * n * kBins);
     if (e == hipSuccess) e = hipMalloc((void **)&dX, sizeof(float) * n * kF);
     if (e == hipSuccess) e = hipMalloc((void **)&dT, sizeof(int32_t) * n);
     if (e == hipSuccess) e = hipMemcpyAsync(dX, X, sizeof(float) * n * kF, hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(dT, T, sizeof(int32_t) * n, hipMemcpyHostToDevice, s->stream);
+    bf16_t *xb = (bf16_t *)s->w_xb.p;
+    int32_t *t32 = (int32_t *)s->w_t32.p;
+    float *dout = (float *)s->w_out.p;
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_rows_to_inputs, dim3((unsigned)std::min<int64_t>(4096, (nb.npad + 255) / 256)), dim3(256),
-                           0, s->stream, n, nb.npad, (const float *)dX, (const int32_t *)dT, nb.xb, nb.t32);
+        hipLaunchKernelGGL(k_rows_to_inputs, dim3((unsigned)std::min<int64_t>(4096, (npad + 255) / 256)), dim3(256),
+                           0, s->stream, n, npad, (const float *)dX, (const int32_t *)dT, xb, t32);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = forward_rows(s, nb.npad, nb.xb, nb.t32, nb.out);
-    if (e == hipSuccess) e = hipMemcpyAsync(out, nb.out, sizeof(float) * n * kBins, hipMemcpyDeviceToHost, s->stream);
+    if (e == hipSuccess) e = forward_rows(s, n, npad, xb, t32, dout);
+    if (e == hipSuccess) e = hipMemcpyAsync(out, dout, sizeof(float) * n * kBins, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     (void)hipFree(dX);
     (void)hipFree(dT);
@@ -1284,46 +1344,46 @@ int surr_predict(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, con
     if (n > (1LL << 31) - 1) return sfail(QW_ERANGE, "too many walks");
     qw_predict_stats ps;
     memset(&ps, 0, sizeof ps);
-    struct Ev {
-        hipEvent_t e = nullptr;
-        ~Ev() { if (e) (void)hipEventDestroy(e); }
-    } ev0, ev1;
-    QS_HIP(hipEventCreate(&ev0.e), "hipEventCreate");
-    QS_HIP(hipEventCreate(&ev1.e), "hipEventCreate");
-    hipEvent_t e0 = ev0.e, e1 = ev1.e;
-    // device scratch released on every return path
-    struct DevBuf {
-        void *p = nullptr;
-        ~DevBuf() { (void)hipFree(p); }
-    } dN, dT, dA, dP, dIdx, dPlain, dNet, dTv;
-    // 1. network on every walk: parameters up, features and forward on the
-    //    device; the bins stay in HBM (nb.out) until the final copy
-    NetBufs nb;
+    for (hipEvent_t &e : s->ev)
+        if (!e) QS_HIP(hipEventCreate(&e), "hipEventCreate");
+    // 1. network on every walk: parameters up, features and forward on the device,
+    //    straight into the caller's device memory, or into HBM until the final copy.
+    //    Nothing waits for it before the re-check's distances are read: the host draws
+    //    the sample and sets up its plain walks meanwhile
+    const int64_t npad = (n + 127) / 128 * 128;
+    float *net = nullptr;
     {
-        hipError_t e = nb.alloc(n);
-        if (e == hipSuccess) e = hipMalloc(&dN.p, 8 * n);
-        if (e == hipSuccess) e = hipMalloc(&dT.p, 8 * n);
-        if (e == hipSuccess) e = hipMalloc(&dA.p, 24 * n);
-        if (e == hipSuccess) e = hipMalloc(&dP.p, 32 * n);
-        if (e == hipSuccess) e = hipEventRecord(e0, s->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(dN.p, N, 8 * n, hipMemcpyHostToDevice, s->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(dT.p, T, 8 * n, hipMemcpyHostToDevice, s->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(dA.p, angles, 24 * n, hipMemcpyHostToDevice, s->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(dP.p, psi0, 32 * n, hipMemcpyHostToDevice, s->stream);
+        hipError_t e = room(s->w_xb, sizeof(bf16_t) * npad * kF);
+        if (e == hipSuccess) e = room(s->w_t32, sizeof(int32_t) * npad);
+        if (e == hipSuccess && !o.out_on_device) e = room(s->w_out, sizeof(float) * n * kBins);
+        if (e == hipSuccess) e = room(s->w_n, 8 * n);
+        if (e == hipSuccess) e = room(s->w_t, 8 * n);
+        if (e == hipSuccess) e = room(s->w_a, 24 * n);
+        if (e == hipSuccess) e = room(s->w_p, 32 * n);
+        net = o.out_on_device ? out : (float *)s->w_out.p;
+        if (e == hipSuccess) e = hipEventRecord(s->ev[0], s->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(s->w_n.p, N, 8 * n, hipMemcpyHostToDevice, s->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(s->w_t.p, T, 8 * n, hipMemcpyHostToDevice, s->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(s->w_a.p, angles, 24 * n, hipMemcpyHostToDevice, s->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(s->w_p.p, psi0, 32 * n, hipMemcpyHostToDevice, s->stream);
         if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_net_inputs, dim3((unsigned)std::min<int64_t>(4096, (nb.npad + 255) / 256)), dim3(256),
-                               0, s->stream, n, nb.npad, (const int64_t *)dN.p, (const int64_t *)dT.p,
-                               (const double *)dA.p, (const double *)dP.p, nb.xb, nb.t32);
+            hipLaunchKernelGGL(k_net_inputs, dim3((unsigned)((npad + 15) / 16)), dim3(64), 0, s->stream, n, npad,
+                               (const int64_t *)s->w_n.p, (const int64_t *)s->w_t.p, (const double *)s->w_a.p,
+                               (const double *)s->w_p.p, (bf16_t *)s->w_xb.p, (int32_t *)s->w_t32.p);
             e = hipGetLastError();
         }
-        if (e == hipSuccess) e = forward_rows(s, nb.npad, nb.xb, nb.t32, nb.out);
-        if (e == hipSuccess) e = hipEventRecord(e1, s->stream);
-        if (e == hipSuccess) e = hipEventSynchronize(e1);
-        if (e != hipSuccess) return sfail(QW_EHIP, "surrogate network pass: %s", hipGetErrorString(e));
+        if (e == hipSuccess) e = forward_rows(s, n, npad, (const bf16_t *)s->w_xb.p, (const int32_t *)s->w_t32.p, net);
+        if (e == hipSuccess) e = hipEventRecord(s->ev[1], s->stream);
+        if (e != hipSuccess) {
+            (void)hipStreamSynchronize(s->stream);
+            return sfail(QW_EHIP, "surrogate network pass: %s", hipGetErrorString(e));
+        }
     }
-    float ms = 0.0f;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    ps.ms_network = ms;
+    // whatever path returns, nothing of this call is still running
+    struct Drain {
+        hipStream_t st;
+        ~Drain() { (void)hipStreamSynchronize(st); }
+    } drain{s->stream};
     int rc = QW_OK;
     // 2. range check and the seeded re-check sample of every chunk
     std::vector<uint8_t> fb(n, 0);
@@ -1361,12 +1421,9 @@ int surr_predict(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, con
             for (int q = 0; q < 3; ++q) a1[3 * j + q] = angles[3 * ids[j] + q];
             for (int q = 0; q < 4; ++q) p1[4 * j + q] = psi0[4 * ids[j] + q];
         }
-        (void)hipFree(dPlain.p);
-        (void)hipFree(dIdx.p);
-        dPlain.p = dIdx.p = nullptr;
-        hipError_t e = hipMalloc(&dPlain.p, sizeof(float) * m * kBins);
-        if (e == hipSuccess) e = hipMalloc(&dIdx.p, sizeof(int64_t) * m);
-        if (e == hipSuccess) e = hipMemcpyAsync(dIdx.p, ids.data(), sizeof(int64_t) * m, hipMemcpyHostToDevice, s->stream);
+        hipError_t e = room(s->w_plain, sizeof(float) * m * kBins);
+        if (e == hipSuccess) e = room(s->w_idx, sizeof(int64_t) * m);
+        if (e == hipSuccess) e = hipMemcpyAsync(s->w_idx.p, ids.data(), sizeof(int64_t) * m, hipMemcpyHostToDevice, s->stream);
         if (e != hipSuccess) return sfail(QW_EHIP, "plain walk buffers: %s", hipGetErrorString(e));
         qw_batch_opts bo;
         memset(&bo, 0, sizeof bo);
@@ -1376,7 +1433,7 @@ int surr_predict(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, con
                                   s->stream, &bt);
         if (r) return sfail(r, "plain walk batch: %s", walk_batch_last_error());
         r = walk_batch_run(bt);
-        if (!r) r = walk_batch_binned(bt, (float *)dPlain.p, 1);
+        if (!r) r = walk_batch_binned(bt, (float *)s->w_plain.p, 1);
         qw_batch_info bi;
         if (!r) r = walk_batch_info(bt, &bi);
         if (!r) msp += bi.last_run_ms;
@@ -1393,18 +1450,18 @@ int surr_predict(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, con
         rc = plain_bins(sample, ps.ms_recheck);
         if (rc) return rc;
         std::vector<double> tv(m);
-        hipError_t e = hipMalloc(&dNet.p, sizeof(float) * m * kBins);
-        if (e == hipSuccess) e = hipMalloc(&dTv.p, sizeof(double) * m);
+        hipError_t e = room(s->w_net, sizeof(float) * m * kBins);
+        if (e == hipSuccess) e = room(s->w_tv, sizeof(double) * m);
         if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)m), dim3(256), 0, s->stream, (const float *)nb.out,
-                               (const int64_t *)dIdx.p, kBins, (float *)dNet.p);
-            hipLaunchKernelGGL(k_tvd, dim3((unsigned)m), dim3(256), 0, s->stream, (const float *)dNet.p,
-                               (const float *)dPlain.p, kBins, (double *)dTv.p);
-            hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)m), dim3(256), 0, s->stream, (const float *)dPlain.p,
-                               (const int64_t *)dIdx.p, kBins, nb.out);
+            hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)m), dim3(256), 0, s->stream, (const float *)net,
+                               (const int64_t *)s->w_idx.p, kBins, (float *)s->w_net.p);
+            hipLaunchKernelGGL(k_tvd, dim3((unsigned)m), dim3(256), 0, s->stream, (const float *)s->w_net.p,
+                               (const float *)s->w_plain.p, kBins, (double *)s->w_tv.p);
+            hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)m), dim3(256), 0, s->stream, (const float *)s->w_plain.p,
+                               (const int64_t *)s->w_idx.p, kBins, net);
             e = hipGetLastError();
         }
-        if (e == hipSuccess) e = hipMemcpyAsync(tv.data(), dTv.p, sizeof(double) * m, hipMemcpyDeviceToHost, s->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(tv.data(), s->w_tv.p, sizeof(double) * m, hipMemcpyDeviceToHost, s->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) return sfail(QW_EHIP, "re-check: %s", hipGetErrorString(e));
         for (size_t j = 0; j < m; ++j) {
@@ -1424,15 +1481,17 @@ int surr_predict(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, con
         rc = plain_bins(fall, ps.ms_fallback);
         if (rc) return rc;
         hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)fall.size()), dim3(256), 0, s->stream,
-                           (const float *)dPlain.p, (const int64_t *)dIdx.p, kBins, nb.out);
+                           (const float *)s->w_plain.p, (const int64_t *)s->w_idx.p, kBins, net);
         QS_HIP(hipGetLastError(), "fallback scatter");
     }
     ps.fallback = (int64_t)fall.size();
-    // 5. the answers: one copy out of HBM
-    QS_HIP(hipMemcpyAsync(out, nb.out, sizeof(float) * n * kBins,
-                          o.out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream),
-           "copy of the bins");
+    // 5. the answers: one copy out of HBM (none when they were asked for on the device)
+    if (!o.out_on_device)
+        QS_HIP(hipMemcpyAsync(out, net, sizeof(float) * n * kBins, hipMemcpyDeviceToHost, s->stream), "copy of the bins");
     QS_HIP(hipStreamSynchronize(s->stream), "stream synchronise");
+    float ms = 0.0f;
+    (void)hipEventElapsedTime(&ms, s->ev[0], s->ev[1]);
+    ps.ms_network = ms;
     if (used_fallback)
         for (int64_t i = 0; i < n; ++i) used_fallback[i] = fb[i];
     if (stats) *stats = ps;
