@@ -633,6 +633,12 @@ template <typename R> __device__ __forceinline__ void finish_walk(const BatchArg
     __syncthreads();
 }
 
+}  // namespace
+}  // namespace qw
+#include "qw_rings.h"
+namespace qw {
+namespace {
+
 // The queue holds the slim kernel's walks first (positions [0, n_slim)), then
 // the other tiled walks ([n_slim, n_tiled)), then the walks held whole
 // ([n_tiled, n)), each part longest-first.  SLIM: rings on their live
@@ -737,6 +743,7 @@ __global__ void k_queue_reset(unsigned int *q) {
     q[2] = 0u;
 }
 
+constexpr int64_t kFewShort = 1024;
 constexpr int kMinTiledSites = 2048;  // shorter rings are always held whole
 constexpr int kMaxMC128 = 4;   // whole-ring sites per thread (register budget)
 constexpr int kMaxMC64 = 9;
@@ -839,7 +846,24 @@ struct qw_batch {
     std::vector<int64_t> p_off;
     int64_t total_sites = 0;
     int64_t n_tiled = 0;
-    int64_t n_slim = 0;  // tiled walks of the slim kernel (the first n_slim queue positions)
+    int64_t n_slim = 0;  // tiled walks of the slim kernel (the first n_slim of the queue)
+    // rings on their live points (qw_rings.h): the first n_wave positions of the order are
+    // walks of one workgroup each, the next n_long advance together; the queue follows
+    int64_t n_wave = 0, n_long = 0;
+    bool few_short = false;  // the walks that fit registers are few: they join the long ones
+    bool points = true;  // false: a variant is forced, or the long walks' planes did not fit
+    struct LongGroup {
+        int32_t K;
+        int64_t first, count;  // positions among the long walks, descending in T
+    };
+    std::vector<LongGroup> groups;
+    std::vector<int64_t> long_off;
+    std::vector<int32_t> long_last;
+    void *d_long[2] = {nullptr, nullptr};
+    double *d_long_norms[2] = {nullptr, nullptr};
+    int64_t *d_long_off = nullptr;
+    int32_t *d_long_last = nullptr;
+    int32_t long_tiles = 0;  // partial norms per walk
     int32_t renorm_every = 0;
     double renorm_tol = 1e-7;
     int32_t links = 0, walls = 0;  // broken links / reflecting ends
@@ -880,6 +904,12 @@ void free_batch(qw_batch *b) {
     (void)hipFree(b->d_queue);
     (void)hipFree(b->d_slots);
     (void)hipFree(b->d_slim_slots);
+    for (int k = 0; k < 2; ++k) {
+        (void)hipFree(b->d_long[k]);
+        (void)hipFree(b->d_long_norms[k]);
+    }
+    (void)hipFree(b->d_long_off);
+    (void)hipFree(b->d_long_last);
     (void)hipFree(b->d_moments);
     (void)hipFree(b->d_bins);
     (void)hipFree(b->d_P);
@@ -919,6 +949,7 @@ BatchArgs make_args(qw_batch *b, const WalkDesc *walks, const int32_t *order, in
 // the slim kernel over queue positions [0, n_slim) (if any), then the general one
 // over the rest (if any); grid: the general kernel's workgroups
 hipError_t enqueue(qw_batch *b, const BatchArgs &A, int grid) {
+    if (A.n < 1) return hipSuccess;
     hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(1), 0, b->stream, b->d_queue);
     if (A.n_slim > 0) {
         const int gs = std::max(1, std::min(b->grid_slim, (int)A.n_slim));
@@ -934,6 +965,78 @@ hipError_t enqueue(qw_batch *b, const BatchArgs &A, int grid) {
             hipLaunchKernelGGL((k_batch<float, kMaxMC64>), dim3(grid), dim3(kBT), 0, b->stream, A);
     }
     return hipGetLastError();
+}
+
+// every block of a group of long walks: visit(t0, tiles of a walk, walks)
+template <typename F> void long_blocks(const qw_batch *b, const qw_batch::LongGroup &g, F visit) {
+    const int32_t *order = b->order.data() + b->n_wave + g.first;
+    const int64_t tmax = b->walks[order[0]].T;
+    int64_t m = g.count;
+    for (int64_t t0 = 0; t0 < tmax; t0 += g.K) {
+        while (b->walks[order[m - 1]].T <= t0) --m;
+        const int64_t points = std::min<int64_t>(t0 + g.K, tmax) + 1;
+        const int tw = 64 * kLongM - g.K;
+        visit(t0, (points + tw - 1) / tw, m);
+    }
+}
+
+hipError_t enqueue_long(qw_batch *b, const BatchArgs &A) {
+    for (const auto &g : b->groups) {
+        LongArgs L{};
+        L.walks = b->d_walks;
+        L.order = b->d_order + b->n_wave + g.first;
+        L.off = b->d_long_off + g.first;
+        L.last_tiles = b->d_long_last + g.first;
+        L.max_tiles = b->long_tiles;
+        L.K = g.K;
+        L.renorm = b->renorm_every;
+        L.tol = b->renorm_tol;
+        int side = 0, prev = 0;
+        const int64_t nb = g.first * (int64_t)b->long_tiles;
+        long_blocks(b, g, [&](int64_t t0, int64_t tiles, int64_t m) {
+            for (int k = 0; k < 2; ++k) {
+                L.psi[k] = b->d_long[side ^ k];
+                L.norms[k] = b->d_long_norms[side ^ k] + nb;
+            }
+            L.t0 = (int32_t)t0;
+            L.ntiles = (int32_t)tiles;
+            L.prev_tiles = prev;
+            const unsigned blocks = (unsigned)((tiles + 3) / 4 * m);
+            if (b->prec == QW_C128) hipLaunchKernelGGL(k_ring_long<double>, dim3(blocks), dim3(256), 0, b->stream, L);
+            else hipLaunchKernelGGL(k_ring_long<float>, dim3(blocks), dim3(256), 0, b->stream, L);
+            prev = (int)tiles;
+            side ^= 1;
+        });
+        for (int k = 0; k < 2; ++k) {
+            L.psi[k] = b->d_long[k];
+            L.norms[k] = b->d_long_norms[k] + nb;
+        }
+        if (b->prec == QW_C128)
+            hipLaunchKernelGGL(k_ring_long_end<double>, dim3((unsigned)g.count), dim3(kBT), 0, b->stream, L, A);
+        else
+            hipLaunchKernelGGL(k_ring_long_end<float>, dim3((unsigned)g.count), dim3(kBT), 0, b->stream, L, A);
+    }
+    return hipGetLastError();
+}
+
+// a run: the walks on their live points, then the queue
+hipError_t enqueue_run(qw_batch *b) {
+    const int64_t np = b->n_wave + b->n_long;
+    const BatchArgs A = make_args(b, b->d_walks, b->d_order + np, (int32_t)(b->n - np), (int32_t)b->n_tiled, (int32_t)b->n_slim);
+    hipError_t e = b->n_long > 0 ? enqueue_long(b, A) : hipSuccess;
+    if (e == hipSuccess && b->n_wave > 0) {
+        BatchArgs W = A;
+        W.order = b->d_order;
+        const dim3 grid((unsigned)b->n_wave);
+        if (b->prec == QW_C128)
+            hipLaunchKernelGGL((k_ring_wave<double, 1>), grid, dim3(128), wave_lds(1, 8, b->nbins), b->stream, W);
+        else if (b->n_wave < kFewWaves)
+            hipLaunchKernelGGL((k_ring_wave<float, 1>), grid, dim3(128), wave_lds(1, 4, b->nbins), b->stream, W);
+        else
+            hipLaunchKernelGGL((k_ring_wave<float, 2>), grid, dim3(64), wave_lds(2, 4, b->nbins), b->stream, W);
+        e = hipGetLastError();
+    }
+    return e == hipSuccess ? enqueue(b, A, b->grid) : e;
 }
 
 int persistent_grid(int prec, int64_t n, bool slim = false) {
@@ -974,8 +1077,10 @@ bool walk_sub(const qw_batch *b, const WalkDesc &w) {
 // the updates the kernel performs: on the live sublattice half of the cone's
 // (at step t, t + 2 of its 2t + 3 offsets are live: counting half is low by at
 // most one site per step)
+bool walk_wave(const qw_batch *b, const WalkDesc &w);
+bool walk_long(const qw_batch *b, const WalkDesc &w);
 double walk_performed(const qw_batch *b, const WalkDesc &w) {
-    return walk_sub(b, w) ? 0.5 * walk_work(w) : walk_work(w);
+    return walk_wave(b, w) || walk_long(b, w) || walk_sub(b, w) ? 0.5 * walk_work(w) : walk_work(w);
 }
 
 // whether the slim kernel runs the walk: on its live sublattice with 128-slot tiles,
@@ -984,8 +1089,19 @@ bool walk_slim(const qw_batch *b, const WalkDesc &w) {
     return walk_sub(b, w) && kCfgMT[w.cfg] == 2 && sub_slots(w, kCfgK[w.cfg]) <= kSlimSlots;
 }
 
-// the queue order: the slim kernel's walks, the other tiled walks, the walks held
-// whole, each part longest-first; sets n_tiled and n_slim
+// walks on their live points: rotation frame (the cone never wraps), both parities
+// not asked for; one workgroup in registers, or (too long for that, or with every P
+// kept) a block of steps at a time
+bool walk_wave(const qw_batch *b, const WalkDesc &w) {
+    return b->points && w.cfg >= 0 && w.rot && !b->full_lattice && !b->keep && !b->few_short && w.T <= kWaveMaxT;
+}
+bool walk_long(const qw_batch *b, const WalkDesc &w) {
+    return b->points && w.cfg >= 0 && w.rot && !b->full_lattice && w.T > 0 && !walk_wave(b, w);
+}
+
+// the order: walks on their live points (in registers, then the long ones by block
+// depth), then the queue: the slim kernel's walks, the other tiled walks, the walks held
+// whole; each part longest-first.  Sets the parts' sizes and the long walks' plan.
 void build_order(qw_batch *b) {
     const int64_t n = b->n;
     b->order.resize(n);
@@ -993,18 +1109,73 @@ void build_order(qw_batch *b) {
     std::vector<double> work(n);
     std::vector<int> part(n);
     for (int64_t i = 0; i < n; ++i) {
-        work[i] = walk_work(b->walks[i]);
-        part[i] = b->walks[i].cfg < 0 ? 2 : (walk_slim(b, b->walks[i]) ? 0 : 1);
+        const WalkDesc &w = b->walks[i];
+        work[i] = walk_wave(b, w) || walk_long(b, w) ? w.T : walk_work(w);
+        part[i] = walk_wave(b, w) ? 0 : walk_long(b, w) ? kCfgK[w.cfg] : w.cfg < 0 ? 1002 : walk_slim(b, w) ? 1000 : 1001;
     }
     std::stable_sort(b->order.begin(), b->order.end(), [&](int32_t a, int32_t c) {
         if (part[a] != part[c]) return part[a] < part[c];
         return work[a] > work[c];
     });
-    b->n_tiled = b->n_slim = 0;
+    b->n_tiled = b->n_slim = b->n_wave = b->n_long = 0;
     for (int64_t i = 0; i < n; ++i) {
-        b->n_tiled += part[i] < 2;
-        b->n_slim += part[i] == 0;
+        b->n_wave += part[i] == 0;
+        b->n_long += part[i] > 0 && part[i] < 1000;
+        b->n_tiled += part[i] == 1000 || part[i] == 1001;
+        b->n_slim += part[i] == 1000;
     }
+    b->groups.clear();
+    b->long_off.assign(b->n_long + 1, 0);
+    b->long_last.assign(b->n_long, 0);
+    b->long_tiles = 1;
+    for (int64_t p = 0; p < b->n_long; ++p) {
+        const int32_t wi = b->order[b->n_wave + p];
+        const WalkDesc &w = b->walks[wi];
+        b->long_off[p + 1] = b->long_off[p] + 2 * ((int64_t)w.T + 1);
+        if (b->groups.empty() || b->groups.back().K != part[wi]) b->groups.push_back({part[wi], p, 0});
+        b->groups.back().count++;
+    }
+    for (const auto &g : b->groups)
+        long_blocks(b, g, [&](int64_t t0, int64_t tiles, int64_t m) {
+            b->long_tiles = std::max<int32_t>(b->long_tiles, (int32_t)tiles);
+            for (int64_t p = m - 1; p >= 0 && b->walks[b->order[b->n_wave + g.first + p]].T <= t0 + g.K; --p)
+                b->long_last[g.first + p] = (int32_t)tiles;
+        });
+}
+
+// device memory of the long walks' plan (build_order), and its tables; any earlier
+// plan's is released first
+hipError_t upload_long(qw_batch *b) {
+    for (int k = 0; k < 2; ++k) {
+        (void)hipFree(b->d_long_norms[k]);
+        b->d_long_norms[k] = nullptr;
+    }
+    (void)hipFree(b->d_long_off);
+    (void)hipFree(b->d_long_last);
+    b->d_long_off = nullptr;
+    b->d_long_last = nullptr;
+    if (b->n_long == 0) return hipSuccess;
+    const size_t esz = b->prec == QW_C128 ? 16 : 8;
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) {
+        if (!b->d_long[k]) e = hipMalloc(&b->d_long[k], esz * (size_t)b->long_off[b->n_long]);
+        if (e == hipSuccess) e = hipMalloc((void **)&b->d_long_norms[k], sizeof(double) * (size_t)b->long_tiles * b->n_long);
+    }
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_long_off, sizeof(int64_t) * (b->n_long + 1));
+    if (e == hipSuccess) e = hipMalloc((void **)&b->d_long_last, sizeof(int32_t) * b->n_long);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->d_long_off, b->long_off.data(), sizeof(int64_t) * (b->n_long + 1), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->d_long_last, b->long_last.data(), sizeof(int32_t) * b->n_long, hipMemcpyHostToDevice, b->stream);
+    return e;
+}
+
+// the largest ring the queue runs through the slot buffers
+int64_t queue_sites(const qw_batch *b, bool every) {
+    int64_t m = 0;
+    for (const auto &w : b->walks)
+        if (w.cfg >= 0 && (every || !(walk_wave(b, w) || walk_long(b, w)))) m = std::max<int64_t>(m, w.N);
+    return m;
 }
 
 }  // namespace
@@ -1056,7 +1227,7 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
     const int mmax = prec == QW_C128 ? kMaxMC128 : kMaxMC64;
     b->walks.resize(n);
     b->p_off.resize(n);
-    int64_t maxN_tiled = 0, off = 0;
+    int64_t off = 0;
     for (int64_t i = 0; i < n; ++i) {
         WalkDesc &w = b->walks[i];
         memset(&w, 0, sizeof w);
@@ -1137,7 +1308,6 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
         } else {
             w.cfg = 0;  // variant assigned below, once the tuning cache is read
             w.m = 0;
-            maxN_tiled = std::max<int64_t>(maxN_tiled, N[i]);
         }
         w.p_off = off;
         b->p_off[i] = off;
@@ -1167,8 +1337,31 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
             if (w.cfg >= 0) w.cfg = b->bucket_cfg[size_bucket(w.N)];
     }
     for (int64_t i = 0; i < n; ++i) b->walks[i].p_off = b->p_off[i];
-    b->slot_elems = maxN_tiled;
+    b->points = o.tiled_variant == 0;
+    {
+        // a walk in registers lasts its steps in one wave (0.45 ms at T = 2000): a few of
+        // them cost a launch of that length, and nothing among the long walks' launches
+        int64_t n_wave = 0, n_long = 0;
+        for (const auto &w : b->walks) {
+            n_wave += walk_wave(b, w);
+            n_long += walk_long(b, w);
+        }
+        b->few_short = n_long > 0 && n_wave < kFewShort;
+    }
+    b->slot_elems = queue_sites(b, false);
     build_order(b);
+    if (upload_long(b) != hipSuccess) {
+        // no room for every long walk's planes at once: one workgroup per walk
+        (void)hipGetLastError();
+        for (int k = 0; k < 2; ++k) {
+            (void)hipFree(b->d_long[k]);
+            b->d_long[k] = nullptr;
+        }
+        b->points = false;
+        b->slot_elems = queue_sites(b, false);
+        build_order(b);
+        (void)upload_long(b);
+    }
     b->grid = persistent_grid(prec, n);
     b->grid_slim = persistent_grid(prec, n, true);
     const size_t esz = prec == QW_C128 ? 16 : 8;
@@ -1184,8 +1377,8 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
         return true;
     };
     bool ok = alloc((void **)&b->d_walks, sizeof(WalkDesc) * n) && alloc((void **)&b->d_order, sizeof(int32_t) * n) &&
-              alloc((void **)&b->d_queue, 256) && alloc(&b->d_slots, (size_t)b->grid * 4 * maxN_tiled * esz) &&
-              alloc(&b->d_slim_slots, (size_t)b->grid_slim * 4 * kSlimSlots * esz) &&
+              alloc((void **)&b->d_queue, 256) && alloc(&b->d_slots, (size_t)b->grid * 4 * b->slot_elems * esz) &&
+              alloc(&b->d_slim_slots, b->n_slim > 0 ? (size_t)b->grid_slim * 4 * kSlimSlots * esz : 0) &&
               alloc((void **)&b->d_moments, sizeof(double) * 3 * n) &&
               (b->nbins == 0 || alloc((void **)&b->d_bins, sizeof(float) * b->nbins * n)) &&
               (!b->keep || alloc((void **)&b->d_P, sizeof(double) * off));
@@ -1212,12 +1405,11 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
 
 int walk_batch_run(qw_batch_t b) {
     if (!b) return bfail(QW_EINVAL, "batch handle is NULL");
-    const BatchArgs A = make_args(b, b->d_walks, b->d_order, (int32_t)b->n, (int32_t)b->n_tiled, (int32_t)b->n_slim);
     QB_HIP(hipEventRecord(b->ev[0], b->stream), "hipEventRecord");
     if (b->use_graph) {
         if (!b->gexec) {
             QB_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-            hipError_t e = enqueue(b, A, b->grid);
+            hipError_t e = enqueue_run(b);
             hipGraph_t g = nullptr;
             hipError_t e2 = hipStreamEndCapture(b->stream, &g);
             if (e != hipSuccess || e2 != hipSuccess) {
@@ -1230,7 +1422,7 @@ int walk_batch_run(qw_batch_t b) {
         }
         QB_HIP(hipGraphLaunch(b->gexec, b->stream), "hipGraphLaunch");
     } else {
-        QB_HIP(enqueue(b, A, b->grid), "batch kernel launch");
+        QB_HIP(enqueue_run(b), "batch kernel launch");
     }
     QB_HIP(hipEventRecord(b->ev[1], b->stream), "hipEventRecord");
     return QW_OK;
@@ -1308,6 +1500,28 @@ int walk_batch_info(qw_batch_t b, qw_batch_info *out) {
 int walk_batch_tune(qw_batch_t b, int32_t samples, int32_t save) {
     if (!b) return bfail(QW_EINVAL, "batch handle is NULL");
     if (samples < 1) samples = 8;
+    // the runs time the queue's kernel on every tiled walk: slot buffers for the largest
+    struct Slots {
+        qw_batch *b;
+        void *kept;
+        int64_t elems;
+        void restore() {
+            if (b->d_slots != kept) (void)hipFree(b->d_slots);
+            b->d_slots = kept;
+            b->slot_elems = elems;
+        }
+        ~Slots() { restore(); }
+    } slots{b, b->d_slots, b->slot_elems};
+    if (queue_sites(b, true) > b->slot_elems) {
+        void *p = nullptr;
+        const int64_t m = queue_sites(b, true);
+        if (hipMalloc(&p, (size_t)b->grid * 4 * m * (b->prec == QW_C128 ? 16 : 8)) != hipSuccess) {
+            (void)hipGetLastError();
+            return bfail(QW_ENOMEM, "hipMalloc for tuning failed");
+        }
+        b->d_slots = p;
+        b->slot_elems = m;
+    }
     // per bucket: the tiled walks of the bucket, a spread sample by work
     std::vector<int32_t> bucket_walks[3];
     for (int64_t i = 0; i < b->n; ++i)
@@ -1375,9 +1589,12 @@ int walk_batch_tune(qw_batch_t b, int32_t samples, int32_t save) {
         b->bucket_cfg[bk] = best;
         for (auto i : v) b->walks[i].cfg = best;
     }
-    // the variants chosen decide which walks the slim kernel takes: new queue order,
-    // and a new graph at the next run (the old one holds the old part sizes)
+    // the variants chosen decide which walks the slim kernel takes and the long walks'
+    // block depths: new order, and a new graph at the next run (the old one holds the
+    // old part sizes)
+    slots.restore();
     build_order(b);
+    QB_HIP(upload_long(b), "the long walks' plan");
     QB_HIP(hipMemcpyAsync(b->d_walks, b->walks.data(), sizeof(WalkDesc) * b->n, hipMemcpyHostToDevice, b->stream),
            "upload of the walk table");
     QB_HIP(hipMemcpyAsync(b->d_order, b->order.data(), sizeof(int32_t) * b->n, hipMemcpyHostToDevice, b->stream),
