@@ -192,30 +192,7 @@ template <typename R> __device__ __forceinline__ double abs2d(cv<R> v) {
 }
 
 // ---------------------------------------------------------------- whole ring
-// Broken links of a ring held whole (RB): bit i tells whether the link from site
-// j*M + i - 1 to the next site (owned by the former, the start site of a move
-// along +1) is broken in the shift pending at step s, i.e. at step s - 1
-// (none at s = 0).  One Philox4x32-10 call per owner site and step (counter:
-// site, 0, step, realization; word 0), as for a single walk on a ring.
-template <int M>
-__device__ __forceinline__ uint32_t whole_links(const WalkDesc &w, const BatchArgs &A, int j, int cnt, int s) {
-    uint32_t lk = 0;  // bit i: lk[i]
-    if (s < 1) return lk;
-#pragma unroll 1
-    for (int i = 0; i <= cnt; ++i) {
-        int owner = j * M + i - 1;
-        owner = owner < 0 ? owner + w.N : owner;
-        bool b = A.walls && owner == w.N - 1;
-        if (!b && A.link_thr != 0) {
-            const uint4 o = philox4((uint32_t)owner, 0u, (uint32_t)(s - 1), w.realization, A.key0, A.key1);
-            b = (uint64_t)o.x < A.link_thr;
-        }
-        lk |= (b ? 1u : 0u) << i;
-    }
-    return lk;
-}
-
-template <typename R, int M, typename CN, bool RB = false>
+template <typename R, int M, typename CN>
 __device__ __forceinline__ void walk_whole(const WalkDesc &w, const BatchArgs &A, cv<R> (*L0)[kBT], cv<R> (*L1)[kBT],
                            BinAcc *s_bins, double (*s_norm)[kWaves], SiteAcc &acc) {
     const int N = w.N;
@@ -288,8 +265,6 @@ __device__ __forceinline__ void walk_whole(const WalkDesc &w, const BatchArgs &A
         __syncthreads();
         if (active && (s == w.T || dmin <= s + 2)) {
             const cv<R> left = L0[p][jl], right = L1[p][jr];
-            uint32_t lk = 0;
-            if constexpr (RB) lk = whole_links<M>(w, A, j, cnt, s);
             if (s < w.T) {
                 // in place, ascending m: a0[m-1] is carried, a1[m+1] is still old
                 cv<R> prev = left;
@@ -297,11 +272,6 @@ __device__ __forceinline__ void walk_whole(const WalkDesc &w, const BatchArgs &A
                 for (int m = 0; m < M; ++m) {
                     cv<R> g0 = prev;
                     cv<R> g1 = (m + 1 < M && m + 1 < cnt) ? a1[m + 1 < M ? m + 1 : m] : right;
-                    if constexpr (RB) {
-                        // a broken link reflects: the opposite component of the site itself
-                        if ((lk >> m) & 1u) g0 = a1[m];
-                        if ((lk >> (m + 1)) & 1u) g1 = a0[m];
-                    }
                     prev = a0[m];
                     cn.apply(g0, g1, a0[m], a1[m]);
                 }
@@ -311,10 +281,6 @@ __device__ __forceinline__ void walk_whole(const WalkDesc &w, const BatchArgs &A
                     if (m < cnt) {
                         cv<R> g0 = m == 0 ? left : a0[m == 0 ? 0 : m - 1];
                         cv<R> g1 = (m + 1 < M && m + 1 < cnt) ? a1[m + 1 < M ? m + 1 : m] : right;
-                        if constexpr (RB) {
-                            if ((lk >> m) & 1u) g0 = a1[m];
-                            if ((lk >> (m + 1)) & 1u) g1 = a0[m];
-                        }
                         const double pr = abs2d<R>(g0) + abs2d<R>(g1);
                         const int x = j * M + m;
                         acc.add(pr, ring_offset(x, w.x0, N), N, A.nbins, s_bins);
@@ -633,6 +599,186 @@ template <typename R> __device__ __forceinline__ void finish_walk(const BatchArg
     __syncthreads();
 }
 
+// ---------------------------------------------------------------- broken links
+// Rings and segments whose links break (every walk of such a batch), one workgroup
+// each, M sites per thread as walk_whole; the coin is the full SU(2) one.  A thread
+// draws the links its own sites own (the one to the right of each) at every step --
+// Philox4x32-10, counter (site, 0, step, realization), word 0, as a single walk on a
+// ring -- and publishes the last with its edge values.  The draws are the time
+// (quarter-rate 32-bit products): what a round makes of the site alone is kept in
+// registers and what it makes of the step alone is scalar, which leaves 15 of the
+// generator's 20 products; and the kernel holds this path only, so two
+// workgroups share a compute unit, one's edge waves idling under the other's work.
+// 1024 segments of 2001 sites, 1000 steps: complex128 7.6 -> 3.7 ms, complex64
+// 8.1 -> 3.3 ms; six waves per SIMD in complex128 (a few spilled registers; four
+// without 3.85 ms), four in complex64 (three 4.3 ms).
+struct SiteDraw {
+    uint32_t h1, l1, l0;  // second round's product of word 2, first round's low product of word 0
+};
+constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u, kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
+__device__ __forceinline__ SiteDraw site_draw(uint32_t site, uint32_t realization, uint32_t key1) {
+    const uint64_t p0 = (uint64_t)kPhiloxM0 * site, p1 = (uint64_t)kPhiloxM1 * ((uint32_t)(p0 >> 32) ^ realization ^ key1);
+    return SiteDraw{(uint32_t)(p1 >> 32), (uint32_t)p1, (uint32_t)p0};
+}
+// word 0 at (site, 0, step, realization): rounds 1 and 2 from site_draw and the step
+__device__ __forceinline__ uint32_t site_word(const SiteDraw &d, uint32_t step, uint32_t key0, uint32_t key1) {
+    const uint64_t u = (uint64_t)kPhiloxM1 * step, v = (uint64_t)kPhiloxM0 * ((uint32_t)(u >> 32) ^ key0);  // uniform
+    uint32_t k0 = key0 + kPhiloxW0, k1 = key1 + kPhiloxW1;
+    uint32_t c0 = d.h1 ^ ((uint32_t)u ^ k0), c1 = d.l1, c2 = d.l0 ^ ((uint32_t)(v >> 32) ^ k1), c3 = (uint32_t)v;
+#pragma unroll
+    for (int r = 2; r < 10; ++r) {
+        k0 += kPhiloxW0;
+        k1 += kPhiloxW1;
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * c0, p1 = (uint64_t)kPhiloxM1 * c2;
+        c0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+        c1 = (uint32_t)p1;
+        c2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        c3 = (uint32_t)p0;
+    }
+    return c0;
+}
+
+template <typename R, int M>
+__device__ __forceinline__ void walk_links(const WalkDesc &w, const BatchArgs &A, cv<R> (*L0)[kBT], cv<R> (*L1)[kBT],
+                                           unsigned char (*Lk)[kBT], BinAcc *s_bins, double (*s_norm)[kWaves], SiteAcc &acc) {
+    const int N = w.N;
+    const int j = threadIdx.x;
+    const int nl = (N + M - 1) / M;
+    const bool active = j < nl;
+    const int cnt = active ? min(M, N - j * M) : 0;
+    const int jl = j == 0 ? nl - 1 : j - 1;
+    const int jr = j + 1 >= nl ? 0 : j + 1;
+    Coin2<R> cn;
+    load_coin<R>(w, cn);
+    const int p0 = wrapN((int64_t)w.x0 - 1, N), p1 = wrapN((int64_t)w.x0 + 1, N);
+    cv<R> a0[M], a1[M];
+    SiteDraw dr[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int x = j * M + m;
+        a0[m] = czero<R>();
+        a1[m] = czero<R>();
+        if (m < cnt && x == p0) { a0[m].x = (R)w.pre[0]; a0[m].y = (R)w.pim[0]; }
+        if (m < cnt && x == p1) { a1[m].x = (R)w.pre[1]; a1[m].y = (R)w.pim[1]; }
+        dr[m] = site_draw((uint32_t)x, w.realization, A.key1);
+    }
+    // waves off the cone keep their zeros and draw nothing, as in walk_whole (a link
+    // between two sites off it moves only zeros)
+    int dmin = 0;
+    {
+        const int wlo = (j >> 6) * 64 * M;
+        const int whi = min(N, wlo + 64 * M) - 1;
+        auto ring_dist = [&](int x) {
+            const int d = x > w.x0 ? x - w.x0 : w.x0 - x;
+            return d < N - d ? d : N - d;
+        };
+        if (wlo >= N) dmin = N;
+        else if (w.x0 < wlo || w.x0 > whi) dmin = min(ring_dist(wlo), ring_dist(whi));
+        dmin = __builtin_amdgcn_readfirstlane(dmin);
+    }
+    int npar = 0;
+    for (int s = 0; s <= w.T; ++s) {
+        const int p = s & 1;
+        if (A.renorm_every > 0 && s > 0 && s < w.T && s % A.renorm_every == 0) {
+            double part = 0.0;
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+                if (m < cnt) part += abs2d<R>(a0[m]) + abs2d<R>(a1[m]);
+            part = wave_sum64(part);
+            if ((threadIdx.x & 63) == 0) s_norm[npar][threadIdx.x >> 6] = part;
+            __syncthreads();
+            const double nrm = sum_waves(s_norm[npar]);
+            npar ^= 1;
+            if (fabs(nrm - 1.0) > A.renorm_tol) {
+                const R sc = (R)(1.0 / sqrt(nrm));
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    a0[m] = cscale<R>(a0[m], sc);
+                    a1[m] = cscale<R>(a1[m], sc);
+                }
+            }
+        }
+        // bit m: the link from site j*M + m - 1 to the next is broken in the shift pending at
+        // step s, that of step s - 1 (none at s = 0)
+        uint32_t lk = 0;
+        const bool near = dmin <= s + 2;
+        if (near && s > 0) {
+            if (A.link_thr != 0) {
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+                    lk |= ((uint64_t)site_word(dr[m], (uint32_t)(s - 1), A.key0, A.key1) < A.link_thr ? 2u : 0u) << m;
+            }
+            if (A.walls && j == nl - 1) lk |= 1u << cnt;
+        }
+        if (active) {
+            cv<R> last = a0[0];
+#pragma unroll
+            for (int m = 1; m < M; ++m)
+                if (m < cnt) last = a0[m];
+            L0[p][j] = last;
+            L1[p][j] = a1[0];
+            Lk[p][j] = (unsigned char)((lk >> cnt) & 1u);
+        }
+        __syncthreads();
+        if (active && (s == w.T || near)) {
+            const cv<R> left = L0[p][jl], right = L1[p][jr];
+            lk |= Lk[p][jl];
+            if (s < w.T) {
+                cv<R> prev = left;
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    cv<R> g0 = prev;
+                    cv<R> g1 = (m + 1 < M && m + 1 < cnt) ? a1[m + 1 < M ? m + 1 : m] : right;
+                    // a broken link reflects: the opposite component of the site itself
+                    if ((lk >> m) & 1u) g0 = a1[m];
+                    if ((lk >> (m + 1)) & 1u) g1 = a0[m];
+                    prev = a0[m];
+                    cn.apply(g0, g1, a0[m], a1[m]);
+                }
+            } else {
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    if (m < cnt) {
+                        cv<R> g0 = m == 0 ? left : a0[m == 0 ? 0 : m - 1];
+                        cv<R> g1 = (m + 1 < M && m + 1 < cnt) ? a1[m + 1 < M ? m + 1 : m] : right;
+                        if ((lk >> m) & 1u) g0 = a1[m];
+                        if ((lk >> (m + 1)) & 1u) g1 = a0[m];
+                        const double pr = abs2d<R>(g0) + abs2d<R>(g1);
+                        const int x = j * M + m;
+                        acc.add(pr, ring_offset(x, w.x0, N), N, A.nbins, s_bins);
+                        if (A.P) A.P[w.p_off + x] = pr;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// block b: the walk at queue position b
+template <typename R, int MMAX> __global__ __launch_bounds__(kBT, sizeof(R) == 8 ? 6 : 4) void k_links(BatchArgs A) {
+    __shared__ BinAcc s_bins[kMaxBins];
+    __shared__ double s_red[3][kWaves];
+    __shared__ double s_norm[2][kWaves];
+    __shared__ cv<R> L0[2][kBT];
+    __shared__ cv<R> L1[2][kBT];
+    __shared__ unsigned char Lk[2][kBT];
+    for (int i = threadIdx.x; i < A.nbins; i += kBT) s_bins[i] = 0;
+    const int wi = A.order[blockIdx.x];
+    const WalkDesc &w = A.walks[wi];
+    SiteAcc acc;
+    switch (w.m) {
+#define QW_LINKS_CASE(MM)                                                                                                   \
+    case MM:                                                                                                                \
+        if constexpr (MM <= MMAX) walk_links<R, MM <= MMAX ? MM : 1>(w, A, L0, L1, Lk, s_bins, s_norm, acc);               \
+        break;
+        QW_LINKS_CASE(1) QW_LINKS_CASE(2) QW_LINKS_CASE(3) QW_LINKS_CASE(4) QW_LINKS_CASE(5)
+        QW_LINKS_CASE(6) QW_LINKS_CASE(7) QW_LINKS_CASE(8) QW_LINKS_CASE(9)
+#undef QW_LINKS_CASE
+    default: break;
+    }
+    finish_walk<R>(A, wi, acc, s_bins, s_red);
+}
+
 }  // namespace
 }  // namespace qw
 #include "qw_rings.h"
@@ -720,8 +866,8 @@ __global__ __launch_bounds__(kBT) void k_batch(BatchArgs A) {
 #define QW_WHOLE_CASE(MM)                                                                                  \
             case MM:                                                                                           \
                 if (MM <= MMAX) {                                                                              \
-                    if (A.links) walk_whole<R, (MM <= MMAX ? MM : 1), Coin2<R>, true>(w, A, L0, L1, s_bins, s_norm, acc); \
-                    else if (w.rot) walk_whole<R, (MM <= MMAX ? MM : 1), CoinRot<R>>(w, A, L0, L1, s_bins, s_norm, acc); \
+                    if (w.rot) \
+                        walk_whole<R, (MM <= MMAX ? MM : 1), CoinRot<R>>(w, A, L0, L1, s_bins, s_norm, acc); \
                     else walk_whole<R, (MM <= MMAX ? MM : 1), Coin2<R>>(w, A, L0, L1, s_bins, s_norm, acc);         \
                 }                                                                                              \
                 break;
@@ -958,7 +1104,12 @@ hipError_t enqueue(qw_batch *b, const BatchArgs &A, int grid) {
         else
             hipLaunchKernelGGL((k_batch<float, kMaxMC64, true>), dim3(gs), dim3(kBT), 0, b->stream, A);
     }
-    if (A.n > A.n_slim) {
+    if (A.links) {  // every walk is held whole
+        if (b->prec == QW_C128)
+            hipLaunchKernelGGL((k_links<double, kMaxMC128>), dim3((unsigned)A.n), dim3(kBT), 0, b->stream, A);
+        else
+            hipLaunchKernelGGL((k_links<float, kMaxMC64>), dim3((unsigned)A.n), dim3(kBT), 0, b->stream, A);
+    } else if (A.n > A.n_slim) {
         if (b->prec == QW_C128)
             hipLaunchKernelGGL((k_batch<double, kMaxMC128>), dim3(grid), dim3(kBT), 0, b->stream, A);
         else

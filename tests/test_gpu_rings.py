@@ -99,3 +99,29 @@ def test_against_oracle():
             C = oracle.coin(oracle.SU2, 2, *ang[i])
             ref = oracle.prob(oracle.walk(int(N[i]), 1, inputs.RING, C, (int(x0[i]), 0), psi0[i], int(T[i])))[0]
             assert np.max(np.abs(bins[i] - oracle.bin_ring(ref, x0[i], 64))) <= tol + 1e-6
+
+
+@pytest.mark.parametrize("prec", [qwalk.QW_C128, qwalk.QW_C64])
+@pytest.mark.parametrize("N", [1, 2, 513, 1024, 1025, 2047, 2048])
+@pytest.mark.parametrize("p,walls", [(0.3, True), (0.3, False), (1.0, False), (0.0, True)])
+def test_links_of_a_batch_are_the_single_walks(prec, N, p, walls):
+    """A batched walk with broken links against the single walk of the same realization
+    (another kernel, the same draws and expressions): the same P to the rounding of its
+    two-term sum."""
+    T = min(90, 2 * N)
+    psi0 = inputs.haar_state(np.random.default_rng(N), 2)
+    x0 = N // 3
+    b = qwalk.Batch([N, N], [T, T], [[0.7, 0.4, 1.1]] * 2, [psi0] * 2, [x0] * 2, prec=prec, keep_probabilities=True,
+                    renorm_every=-1, walls=walls, link_p=p, link_seed=9 << 33, realization0=5)
+    b.run()
+    P = b.probabilities()[1]
+    b.destroy()
+    w = qwalk.Walk((N,), inputs.RING, qwalk.SU2, psi0, (x0, 0), prec=prec, theta=0.7, phi=0.4, chi=1.1)
+    w.set_options(renorm_every=0)
+    w.set_broken_links(p, seed=9 << 33, realization=6)
+    w.set_reflecting_walls(walls)
+    w.step(T)
+    ref = w.probabilities()[0]
+    w.destroy()
+    # complex64: the single walk's coin is rounded once from the same fp64 entries
+    assert np.max(np.abs(P - ref)) <= (4 * 2.0 ** -53 if prec == qwalk.QW_C128 else 4 * T * 2.0 ** -24)
