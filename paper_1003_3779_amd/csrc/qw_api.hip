@@ -640,25 +640,25 @@ int run_forward(qw_walk *w, int64_t n) {
     if (w->dim == 1 && w->ring_std && depth > 1 && w->g.Lx <= ring_whole_max_sites(w->prec)) {
         // the whole ring in one workgroup: all n steps in one launch (every
         // site is computed, or, for a walk from one site whose support stays
-        // clear of itself, every site of its live parity; the light-cone box
-        // stays exact bookkeeping)
+        // clear of itself, the points it reaches; the light-cone box stays
+        // exact bookkeeping)
         const int64_t t0 = w->t;
         grow_forward(w, n);
         LaunchInfo li;
         Timed tm(w);
-        int64_t sites = w->g.Lx;
+        int64_t sites = n * t0 + n * (n + 1) / 2;  // of all n steps: points 0 .. t at time t
         hipError_t e = hipErrorNotSupported;
         if (w->pure && !w->rbl_on)
-            e = launch_ring_sub(w->prec, cur_buf(w), oth_buf(w), w->g, w->C, n, w->x0[0], t0, w->stream, &li, &sites);
+            e = launch_ring_cone(w->prec, cur_buf(w), oth_buf(w), w->g, w->C, n, w->x0[0], t0, w->stream, &li);
         if (e == hipErrorNotSupported) {
-            sites = w->g.Lx;
+            sites = w->g.Lx * n;
             e = launch_ring_whole(w->prec, cur_buf(w), oth_buf(w), w->g, w->C, n, w->stream, &li);
         }
         QW_HIP(e, "ring kernel");
-        tm.done(QW_KERNEL_RING_WHOLE, li, (double)sites * w->d * n, state_bytes_of(w, 2 * w->g.Lx));
+        tm.done(QW_KERNEL_RING_WHOLE, li, (double)sites * w->d, state_bytes_of(w, 2 * w->g.Lx));
         w->cur ^= 1;
         w->launches++;
-        w->updates += sites * w->d * n;
+        w->updates += sites * w->d;
         return QW_OK;
     }
     // ---- torus launch choice: begin ----
@@ -833,10 +833,7 @@ hipError_t place_state(qw_walk *w, const double *psi0) {
         w->cone.y0 = (int32_t)w->x0[1];
         return launch_cone_place(w->prec, w->buf[0], w->cone, psi0, w->stream);
     }
-    hipError_t e1 = launch_fill_zero(w->buf[0], w->state_bytes, w->stream);
-    hipError_t e2 = launch_fill_zero(w->buf[1], w->state_bytes, w->stream);
-    hipError_t e3 = launch_place(w->prec, w->buf[0], w->g, w->x0[0], w->x0[1], psi0, w->stream);
-    return e1 != hipSuccess ? e1 : (e2 != hipSuccess ? e2 : e3);
+    return launch_start(w->prec, w->buf[0], w->buf[1], w->g, w->x0[0], w->x0[1], psi0, w->stream);
 }
 
 // The start state and a cleared scratch area: kernels on the walk's stream.

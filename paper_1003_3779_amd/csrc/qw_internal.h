@@ -50,8 +50,9 @@ struct LaunchInfo {
 
 // ---- launchers (qw_kernels.hip); all return a hipError_t ----
 hipError_t launch_fill_zero(void *buf, size_t bytes, hipStream_t s);
-hipError_t launch_place(int prec, void *state, const Geom &g, int64_t x0, int64_t y0,
-                        const double *psi0, hipStream_t s);
+// buffer a := |x0> (x) psi0 (pre-shift), buffer b := 0
+hipError_t launch_start(int prec, void *a, void *b, const Geom &g, int64_t x0, int64_t y0, const double *psi0,
+                        hipStream_t s);
 // one step of U over the output box (in -> out)
 hipError_t launch_step(int prec, int coin_impl, const void *in, void *out, const Geom &g,
                        const Box &out_box, const CoinF64 &C, hipStream_t s, LaunchInfo *info);
@@ -89,13 +90,12 @@ hipError_t launch_ring_whole(int prec, const void *in, void *out, const Geom &g,
                              const CoinF64 &C, int64_t K, hipStream_t s, LaunchInfo *info,
                              const Links *links = nullptr, int64_t t0 = 0);
 
-// K steps of a ring walk started at the single site x0, now at time t0, on its
-// live sublattice (offsets x - x0 of parity 1 + t; the rest of the state is
-// exactly zero), one workgroup; slots (optional) receives the slots it steps.
-// hipErrorNotSupported (nothing launched) unless g is a ring the kernel holds
-// and t0 + K <= (N - 1) / 2.
-hipError_t launch_ring_sub(int prec, const void *in, void *out, const Geom &g, const CoinF64 &C, int64_t K,
-                           int64_t x0, int64_t t0, hipStream_t s, LaunchInfo *info, int64_t *slots);
+// K steps of a ring walk started at the single site x0, now at time t0, on the
+// points it can reach (the rest of the state is exactly zero and written as zeros).
+// hipErrorNotSupported (nothing launched) unless the points fit the kernel and
+// t0 + K <= (N - 1) / 2.
+hipError_t launch_ring_cone(int prec, const void *in, void *out, const Geom &g, const CoinF64 &C, int64_t K,
+                            int64_t x0, int64_t t0, hipStream_t s, LaunchInfo *info);
 
 // launch shape of the torus streaming kernel
 struct StreamTune {
@@ -132,12 +132,13 @@ hipError_t launch_stream2d_wg(int prec, int coin_impl, int table, const void *in
 // of L (the previous step), then the coin: a_{t+1}(y, c) = sum C[c][c'] (S_L a_t)(y, c')
 hipError_t launch_step_rbl(int prec, int coin_impl, const void *in, void *out, const Geom &g, const Box &b,
                            const CoinF64 &C, const Links &L, hipStream_t s, LaunchInfo *info);
-// P(x) and the norm of psi = S_L a (box b), as launch_prob_norm
+// P(x) or the norm of psi = S_L a (box b), as launch_prob_norm
 hipError_t launch_prob_norm_rbl(int prec, const void *state, const Geom &g, const Box &b, double *P, Scratch *scr,
                                 const Links &L, hipStream_t s);
 // psi = S_L a over the whole lattice as complex128 (d, Ly, Lx)
 hipError_t launch_get_state_rbl(int prec, const void *state, const Geom &g, void *out, const Links &L,
                                 hipStream_t s);
+// P(x) over the box into P, or (P null) the norm into scratch->norm
 hipError_t launch_prob_norm(int prec, const void *state, const Geom &g, const Box &psi_box,
                             double *P, Scratch *scr, hipStream_t s);
 // norm of the state (no shift needed: S is a permutation) into scratch->norm

@@ -48,15 +48,28 @@ struct Psi0 {
     double re[4], im[4];
 };
 
+// |x0> (x) psi0: buffer a with the start amplitudes among its zeros, buffer b cleared, one
+// launch (three cost a small walk 15 us of launches)
 template <typename R>
-__global__ void k_place(cv<R> *a, Geom g, int x0, int y0, Psi0 p) {
-    int c = threadIdx.x;
-    if (c >= g.d) return;
-    int x = wrapi(x0 - g.ex[c], g.Lx), y = wrapi(y0 - g.ey[c], g.Ly);
-    cv<R> v;
-    v.x = (R)p.re[c];
-    v.y = (R)p.im[c];
-    a[(int64_t)c * g.ps + (int64_t)y * g.Lx + x] = v;
+__global__ __launch_bounds__(256) void k_start(cv<R> *a, cv<R> *b, int64_t n, Geom g, int x0, int y0, Psi0 p) {
+    int64_t at[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int cc = c < g.d ? c : 0;
+        at[c] = (int64_t)cc * g.ps + (int64_t)wrapi(y0 - g.ey[cc], g.Ly) * g.Lx + wrapi(x0 - g.ex[cc], g.Lx);
+    }
+    const cv<R> z = czero<R>();
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        cv<R> v = z;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (c < g.d && i == at[c]) {
+                v.x = (R)p.re[c];
+                v.y = (R)p.im[c];
+            }
+        a[i] = v;
+        b[i] = z;
+    }
 }
 
 // =====================================================================
@@ -300,98 +313,142 @@ __global__ __launch_bounds__(256) void k_ring_halo(const cv<R> *__restrict__ in,
     }
 }
 
-// The ring coin as k_ring_halo applies it (the same expressions, so the same
-// roundings): real entries (REALC) or complex ones.
-template <typename R, bool REALC> struct HaloCoin {
+// K steps of a ring walk on the points it can reach: started at x0 and at time t0, its
+// amplitudes live at the offsets 2 i - t, i = 0 .. t, and with psi_t at these points
+//     (o0, o1) = C psi_t[i];  psi_{t+1}[i + 1].c0 = o0;  psi_{t+1}[i].c1 = o1.
+// The launcher asks for t0 + K <= (N - 1) / 2: the points never meet around the
+// ring.  They live in LDS; four waves (one per SIMD) each take a quarter of those a
+// round of kRingHalo steps reaches, with kRingHalo more below (c0 comes from below only),
+// M per lane, M as the cone grows, and meet in LDS once a round.  A real coin maps
+// Re psi to Re psi' and Im psi to Im psi': two workgroups, one part each (NP = 1).
+// The same expressions per point as k_ring_halo (bitwise equal); sites off the points
+// are written as zeros.  Bound by the fp64 operations in series of one compute unit: 2001-site
+// Hadamard ring, T = 1000, complex128: 104 us on every live slot at every step, both
+// parts in one workgroup, now 47.
+template <typename R, bool REALC> struct PointCoin {
     R c00r, c00i, c01r, c01i, c10r, c10i, c11r, c11i;
-    __device__ __forceinline__ void apply(cv<R> g0, cv<R> g1, cv<R> &o0, cv<R> &o1) const {
-        if constexpr (REALC) {
-            o0.x = fmaR(c01r, g1.x, c00r * g0.x);
-            o0.y = fmaR(c01r, g1.y, c00r * g0.y);
-            o1.x = fmaR(c11r, g1.x, c10r * g0.x);
-            o1.y = fmaR(c11r, g1.y, c10r * g0.y);
-        } else {
-            o0 = cmac<R>(cmul<R>(c00r, c00i, g0), c01r, c01i, g1);
-            o1 = cmac<R>(cmul<R>(c10r, c10i, g0), c11r, c11i, g1);
-        }
+    __device__ __forceinline__ void apply(const R (&g0)[2], const R (&g1)[2], R (&o0)[2], R (&o1)[2]) const {
+        cv<R> a, b;
+        a.x = g0[0]; a.y = g0[1];
+        b.x = g1[0]; b.y = g1[1];
+        const cv<R> u = cmac<R>(cmul<R>(c00r, c00i, a), c01r, c01i, b), v = cmac<R>(cmul<R>(c10r, c10i, a), c11r, c11i, b);
+        o0[0] = u.x; o0[1] = u.y;
+        o1[0] = v.x; o1[1] = v.y;
+    }
+    __device__ __forceinline__ void apply(const R (&g0)[1], const R (&g1)[1], R (&o0)[1], R (&o1)[1]) const {
+        o0[0] = fmaR(c01r, g1[0], c00r * g0[0]);
+        o1[0] = fmaR(c11r, g1[0], c10r * g0[0]);
     }
 };
 
-// K steps of a ring walk on its live sublattice, one workgroup: the walk was
-// started at x0 and is at time t0, so its pre-shift state is non-zero only at
-// offsets d = x - x0 of parity 1 + t, and |d| <= t + 1.  The launcher asks for
-// t0 + K <= (N - 1) / 2: the support never meets itself around the ring, so
-// the walk is the walk on the line of offsets [-H, H], H = (N + 1) / 2, held
-// as slots (offset 2 j + q - O in slot j, O even) in LDS and, as in
-// k_ring_halo, stepped in four wave windows that meet in LDS every 32 steps
-// (16 halo slots a side: a step spoils one slot on one side of a window,
-// alternately).  Half the sites per step of k_ring_halo, bitwise the same
-// values; the dead offsets are written as zeros.
-template <typename R, int M, bool REALC>
-__global__ __launch_bounds__(256) void k_ring_sub(const cv<R> *__restrict__ in, cv<R> *__restrict__ out, int N,
-                                                  int64_t ps, int x0, int64_t t0, int64_t K, CoinR<R> C) {
-    constexpr int kMax = 32768 / (int)sizeof(cv<R>);  // 2 planes: 64 KiB of LDS
-    constexpr int kHS = kRingHalo / 2;               // halo slots a side per exchange
-    __shared__ cv<R> S0[kMax];
-    __shared__ cv<R> S1[kMax];
-    const int H = (N + 1) / 2, O = (H + 1) & ~1;
-    const int ns = (O + H) / 2 + 2;  // slots (the launcher checks ns <= kMax)
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int q0 = (int)((1 + t0) & 1);
-    for (int j = threadIdx.x; j < ns; j += 256) {
-        const int d = 2 * j + q0 - O;
-        cv<R> v0 = czero<R>(), v1 = czero<R>();
-        if (d >= -(t0 + 1) && d <= t0 + 1) {  // the support, 2 t0 + 3 <= N offsets: no two share a site
-            int x = (x0 + d) % N;
-            x = x < 0 ? x + N : x;
-            v0 = in[x];
-            v1 = in[ps + x];
+// one round of a wave: its window from LDS (points first .. , M per lane), h steps,
+// then its own points [own0, own1) back
+template <typename R, int NP, int M>
+__device__ __forceinline__ void ring_round(R *S0, R *S1, int cap, int first, int live, int own0, int own1, int h,
+                                           const PointCoin<R, NP == 1> &cn, int lane) {
+    R c0[M][NP], c1[M][NP];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int i = first + lane * M + m;
+        const bool in = i >= 0 && i < live;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            c0[m][p] = in ? S0[p * cap + (in ? i : 0)] : (R)0;
+            c1[m][p] = in ? S1[p * cap + (in ? i : 0)] : (R)0;
         }
-        S0[j] = v0;
-        S1[j] = v1;
     }
-    __syncthreads();
-    HaloCoin<R, REALC> cn;
-    cn.c00r = C.re[0]; cn.c00i = C.im[0]; cn.c01r = C.re[1]; cn.c01i = C.im[1];
-    cn.c10r = C.re[2]; cn.c10i = C.im[2]; cn.c11r = C.re[3]; cn.c11i = C.im[3];
-    const int I = (ns + 3) / 4;
-    const int own0 = w * I, own1 = min(ns, own0 + I);
-    const int ws = own0 - kHS;  // first slot of this wave's window (may lie before slot 0)
-    cv<R> c0[M], c1[M];
-    for (int64_t done = 0; done < K; done += kRingHalo) {
-        const int h = K - done < kRingHalo ? (int)(K - done) : kRingHalo;
+    auto step = [&]() {
+        R up[NP];
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int j = ws + lane * M + m;
-            const bool inr = j >= 0 && j < ns;  // past the line's ends: zeros (the cone never gets there)
-            c0[m] = inr ? S0[inr ? j : 0] : czero<R>();
-            c1[m] = inr ? S1[inr ? j : 0] : czero<R>();
-        }
-        sub_tile_steps<R, M, HaloCoin<R, REALC>>(c0, c1, cn, h, (int)((1 + t0 + done) & 1));
-        __syncthreads();  // every window read before any owned slot is overwritten
+        for (int m = M - 1; m >= 0; --m) {  // descending: c0[m + 1] is consumed before it is written
+            R o0[NP], o1[NP];
+            cn.apply(c0[m], c1[m], o0, o1);
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int j = ws + lane * M + m;
-            if (j >= own0 && j < own1) {
-                S0[j] = c0[m];
-                S1[j] = c1[m];
+            for (int p = 0; p < NP; ++p) {
+                if (m == M - 1) up[p] = o0[p];
+                else c0[m + 1][p] = o0[p];
+                c1[m][p] = o1[p];
             }
         }
-        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < NP; ++p) c0[0][p] = lane_from_left(up[p]);
+    };
+    constexpr int kAtOnce = M <= 3 ? 8 : 4;  // one copy of the registers per body (70 us with one per step)
+    int st = 0;
+    for (; st + kAtOnce <= h; st += kAtOnce) {
+#pragma unroll
+        for (int i = 0; i < kAtOnce; ++i) step();
     }
-    const int qT = (int)((1 + t0 + K) & 1);
-    for (int x = threadIdx.x; x < N; x += 256) {
-        int d = x - x0;  // the offset of x in (-N/2, N/2]
-        d = d < 0 ? d + N : d;
-        d = d > N / 2 ? d - N : d;
-        cv<R> v0 = czero<R>(), v1 = czero<R>();
-        if (((d + O - qT) & 1) == 0) {
-            const int j = (d + O - qT) / 2;
-            v0 = S0[j];
-            v1 = S1[j];
+    for (; st < h; ++st) step();
+    __syncthreads();  // every window read before any own point is overwritten
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int i = first + lane * M + m;
+        if (i >= own0 && i < own1) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                S0[p * cap + i] = c0[m][p];
+                S1[p * cap + i] = c1[m][p];
+            }
         }
-        out[x] = v0;
-        out[ps + x] = v1;
+    }
+    __syncthreads();
+}
+
+template <typename R, int NP>
+__global__ __launch_bounds__(256) void k_ring_cone(const R *__restrict__ in, R *__restrict__ out, int N, int64_t ps, int x0,
+                                                   int t0, int K, CoinR<R> C) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char ring_mem[];
+    const int T = t0 + K, cap = T + 1;
+    R *S0 = (R *)ring_mem, *S1 = S0 + NP * cap;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const R *src = in + (NP == 1 ? blockIdx.x : 0);  // this part's words of the (re, im) pairs
+    R *dst = out + (NP == 1 ? blockIdx.x : 0);
+    auto site = [&](int d) {  // of offset d, |d| <= N
+        const int x = x0 + d;
+        return x < 0 ? x + N : (x >= N ? x - N : x);
+    };
+    // psi_t(x, c) = a_t(x - e_c, c)
+    for (int i = threadIdx.x; i <= t0; i += 256) {
+        const int xa = site(2 * i - t0 - 1), xb = site(2 * i - t0 + 1);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            S0[p * cap + i] = src[2 * (int64_t)xa + p];
+            S1[p * cap + i] = src[2 * (ps + xb) + p];
+        }
+    }
+    __syncthreads();
+    PointCoin<R, NP == 1> cn;
+    cn.c00r = C.re[0]; cn.c00i = C.im[0]; cn.c01r = C.re[1]; cn.c01i = C.im[1];
+    cn.c10r = C.re[2]; cn.c10i = C.im[2]; cn.c11r = C.re[3]; cn.c11i = C.im[3];
+    for (int t = t0; t < T; t += kRingHalo) {
+        const int h = min(kRingHalo, T - t), points = t + h + 1, I = (points + 3) / 4;
+        const int own0 = w * I, own1 = min(points, own0 + I), first = own0 - h, need = (I + h + 63) / 64;
+#define QW_ROUND(M) ring_round<R, NP, M>(S0, S1, cap, first, t + 1, own0, own1, h, cn, lane)
+        switch (need) {  // the same for every wave
+        case 1: QW_ROUND(1); break;
+        case 2: QW_ROUND(2); break;
+        case 3: QW_ROUND(3); break;
+        case 4: QW_ROUND(4); break;
+        case 5: QW_ROUND(5); break;
+        case 6: case 7: QW_ROUND(7); break;
+        default: QW_ROUND(9); break;
+        }
+#undef QW_ROUND
+    }
+    // a_T(x, 0) = psi_T(x + 1, 0), a_T(x, 1) = psi_T(x - 1, 1)
+    for (int x = threadIdx.x; x < N; x += 256) {
+        int d = x - x0;
+        d = d < 0 ? d + N : d;
+        d = d > N / 2 ? d - N : d;  // in (-N/2, N/2]
+        const bool odd = ((d + 1 + T) & 1) != 0;
+        const int ia = (d + 1 + T) >> 1, ib = (d - 1 + T) >> 1;
+        const bool oka = !odd && ia >= 0 && ia <= T, okb = !odd && ib >= 0 && ib <= T;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            dst[2 * (int64_t)x + p] = oka ? S0[p * cap + (oka ? ia : 0)] : (R)0;
+            dst[2 * (ps + x) + p] = okb ? S1[p * cap + (okb ? ib : 0)] : (R)0;
+        }
     }
 }
 
@@ -954,17 +1011,19 @@ hipError_t launch_fill_zero(void *buf, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_place(int prec, void *state, const Geom &g, int64_t x0, int64_t y0, const double *psi0,
+hipError_t launch_start(int prec, void *a, void *b, const Geom &g, int64_t x0, int64_t y0, const double *psi0,
                         hipStream_t s) {
     Psi0 p;
     for (int c = 0; c < 4; ++c) {
         p.re[c] = c < g.d ? psi0[2 * c] : 0.0;
         p.im[c] = c < g.d ? psi0[2 * c + 1] : 0.0;
     }
+    const int64_t n = g.ps * g.d;
+    const unsigned blocks = (unsigned)std::min<int64_t>(8192, (n + 255) / 256);
     if (prec == C128)
-        hipLaunchKernelGGL(k_place<double>, dim3(1), dim3(64), 0, s, (double2 *)state, g, (int)x0, (int)y0, p);
+        hipLaunchKernelGGL(k_start<double>, dim3(blocks), dim3(256), 0, s, (double2 *)a, (double2 *)b, n, g, (int)x0, (int)y0, p);
     else
-        hipLaunchKernelGGL(k_place<float>, dim3(1), dim3(64), 0, s, (float2 *)state, g, (int)x0, (int)y0, p);
+        hipLaunchKernelGGL(k_start<float>, dim3(blocks), dim3(256), 0, s, (float2 *)a, (float2 *)b, n, g, (int)x0, (int)y0, p);
     return hipGetLastError();
 }
 
@@ -1092,62 +1151,33 @@ static bool ring_halo_t(int m, const void *in, void *out, const Geom &g, const C
 #undef QW_RING_HALO
 }
 
-// slots per lane of k_ring_sub: the smallest listed M whose window holds a
-// quarter of the slots plus both halos (0: the ring is too long)
-static int ring_sub_m(int prec, int64_t N) {
-    static const int mc128[] = {2, 3, 5}, mc64[] = {2, 3, 5, 9};
-    const int64_t kmax = prec == C128 ? 2048 : 4096;  // slots in 64 KiB of LDS
-    const int64_t H = (N + 1) / 2, O = (H + 1) & ~1LL, ns = (O + H) / 2 + 2;
-    if (N < 3 || ns > kmax) return 0;
-    const int64_t I = (ns + 3) / 4;
-    const int *ms = prec == C128 ? mc128 : mc64;
-    const int nm = prec == C128 ? 3 : 4;
-    for (int i = 0; i < nm; ++i)
-        if (64LL * ms[i] >= I + kRingHalo) return ms[i];
-    return 0;
-}
-
-template <typename R>
-static bool ring_sub_t(int m, const void *in, void *out, const Geom &g, const CoinF64 &C, int x0, int64_t t0,
-                       int64_t K, hipStream_t s) {
-    const bool real = C.im[0] == 0.0 && C.im[1] == 0.0 && C.im[2] == 0.0 && C.im[3] == 0.0;
-#define QW_RING_SUB(MV)                                                                                   \
-    do {                                                                                                  \
-        if (real)                                                                                         \
-            hipLaunchKernelGGL((k_ring_sub<R, MV, true>), dim3(1), dim3(256), 0, s, (const cv<R> *)in,    \
-                               (cv<R> *)out, g.Lx, g.ps, x0, t0, K, to_coin<R>(C));                       \
-        else                                                                                              \
-            hipLaunchKernelGGL((k_ring_sub<R, MV, false>), dim3(1), dim3(256), 0, s, (const cv<R> *)in,   \
-                               (cv<R> *)out, g.Lx, g.ps, x0, t0, K, to_coin<R>(C));                       \
-    } while (0)
-    switch (m) {
-    case 2: QW_RING_SUB(2); return true;
-    case 3: QW_RING_SUB(3); return true;
-    case 5: QW_RING_SUB(5); return true;
-    case 9: if constexpr (sizeof(R) == 4) { QW_RING_SUB(9); return true; } return false;
-    default: return false;
-    }
-#undef QW_RING_SUB
-}
-
-hipError_t launch_ring_sub(int prec, const void *in, void *out, const Geom &g, const CoinF64 &C, int64_t K,
-                           int64_t x0, int64_t t0, hipStream_t s, LaunchInfo *info, int64_t *slots) {
+hipError_t launch_ring_cone(int prec, const void *in, void *out, const Geom &g, const CoinF64 &C, int64_t K, int64_t x0,
+                            int64_t t0, hipStream_t s, LaunchInfo *info) {
     const int64_t N = g.Lx;
-    const int m = ring_sub_m(prec, N);
-    if (m == 0 || g.Ly != 1 || t0 < 0 || K < 1 || t0 + K > (N - 1) / 2 || x0 < 0 || x0 >= N)
+    // (64 KiB of LDS, and a quarter of the points with the halo in 9 per lane)
+    const int64_t points = t0 + K + 1, es = prec == C128 ? 8 : 4;
+    const bool real = C.im[0] == 0.0 && C.im[1] == 0.0 && C.im[2] == 0.0 && C.im[3] == 0.0;
+    const size_t lds = (size_t)(2 * (real ? 1 : 2) * points * es);
+    if (g.Ly != 1 || t0 < 0 || K < 1 || t0 + K > (N - 1) / 2 || x0 < 0 || x0 >= N || lds > 65536 ||
+        (points + 3) / 4 + kRingHalo > 64 * 9)
         return hipErrorNotSupported;
     if (info) {
-        const double bytes = (double)N * 2 * (prec == C128 ? 16.0 : 8.0);
+        const double bytes = (double)N * 2 * 2 * es;
         info->bytes_read = bytes;
         info->bytes_written = bytes;
     }
-    if (slots) {
-        const int64_t H = (N + 1) / 2, O = (H + 1) & ~1LL;
-        *slots = (O + H) / 2 + 2;
+#define QW_RING_CONE(R, NP)                                                                                             \
+    hipLaunchKernelGGL((k_ring_cone<R, NP>), dim3(3 - NP), dim3(256), lds, s, (const R *)in, (R *)out, g.Lx, g.ps,      \
+                       (int)x0, (int)t0, (int)K, to_coin<R>(C))
+    if (prec == C128) {
+        if (real) QW_RING_CONE(double, 1);
+        else QW_RING_CONE(double, 2);
+    } else {
+        if (real) QW_RING_CONE(float, 1);
+        else QW_RING_CONE(float, 2);
     }
-    const bool ok = prec == C128 ? ring_sub_t<double>(m, in, out, g, C, (int)x0, t0, K, s)
-                                 : ring_sub_t<float>(m, in, out, g, C, (int)x0, t0, K, s);
-    return ok ? hipGetLastError() : hipErrorNotSupported;
+#undef QW_RING_CONE
+    return hipGetLastError();
 }
 
 hipError_t launch_ring_whole(int prec, const void *in, void *out, const Geom &g, const CoinF64 &C, int64_t K,
@@ -1381,6 +1411,7 @@ hipError_t launch_prob_norm(int prec, const void *state, const Geom &g, const Bo
         else
             hipLaunchKernelGGL((k_prob<float, 4>), grid, dim3(256), 0, s, (const float2 *)state, g, b, P, scr->partial);
     }
+    if (P) return hipGetLastError();  // P(x) alone: nobody reads the norm
     hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, s, (const double *)scr->partial, nparts, &scr->norm);
     return hipGetLastError();
 }
@@ -1501,6 +1532,7 @@ hipError_t launch_prob_norm_rbl(int prec, const void *state, const Geom &g, cons
             hipLaunchKernelGGL((k_prob_rbl<float, 4>), grid, dim3(256), 0, s, (const float2 *)state, g, b, L, P,
                                scr->partial);
     }
+    if (P) return hipGetLastError();
     hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, s, (const double *)scr->partial, nparts, &scr->norm);
     return hipGetLastError();
 }
