@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 namespace qw {
@@ -76,39 +77,40 @@ struct GemmArgs {
     int ldcb;
 };
 
-constexpr int kBM = 128, kBN = 128, kBK = 64, kLdsRow = kBK + 8;  // +8 bf16: 16-byte aligned, spread rows
-constexpr int kPF = 2;                                           // K tiles in flight
+constexpr int kBM = 128, kBK = 64;  // (kBM: the largest tile side)
 constexpr int kKAlign = 32;                                      // K must be a multiple of this
 constexpr unsigned kNoLoad = 0x80000000u;                        // an offset past any operand's range
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const bf16_t *p, int rows, int ld) {
     // descriptor word 3 of the gfx9 family: 32-bit data format, no swizzle, no stride
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(p), (short)0, rows * ld * 2, 0x00020000);
 }
 
-// One launch runs one product, or two independent ones side by side (blocks
-// [0, nb0) the first, gx0 blocks per row of tiles; the rest the second): the
-// batch-1024 training products have 64 tiles each, a quarter of the chip.
-// NW waves per 128 x 128 tile: 16 (each 32 x 32 outputs, four per SIMD: some
-// waves' LDS reads run under the others' MFMAs) as launched; 8 (64 x 32, two per
-// SIMD) and 4 (64 x 64, one per SIMD; fewer LDS reads per MFMA) measured slower
-// at every launch size the network uses.
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_gemm_nt(GemmArgs g0, GemmArgs g1, int nb0, int gx0, int gx1) {
-    static_assert(NW == 4 || NW == 8 || NW == 16, "four, eight or sixteen waves per tile");
-    constexpr int TI = NW == 16 ? 1 : 2, WM = 32 * TI;                 // 32-row tiles per wave, wave height
-    constexpr int TJ = NW == 4 ? 2 : 1, WN = 32 * TJ, NWN = kBN / WN;  // 32-column tiles per wave, wave width
-    constexpr int RPP = 8 * NW, NH = kBM / RPP;                       // staging rows per pass, passes
-    __shared__ bf16_t sA[2][kBM * kLdsRow];
-    __shared__ bf16_t sB[2][kBN * kLdsRow];
-    const bool second = (int)blockIdx.x >= nb0;
-    const GemmArgs g = second ? g1 : g0;
-    const int bl = second ? (int)blockIdx.x - nb0 : (int)blockIdx.x, gx = second ? gx1 : gx0;
+// A BT x BT tile (128 or 64) per block, a wave per 32 x 32 outputs: 16 waves, four per
+// SIMD, on 128 (some waves' LDS reads run under the others' MFMAs; 64 x 32 and 64 x 64
+// outputs per wave measured slower at every launch size the network uses), four waves
+// on 64.  PF K tiles in flight per block.  The K order of an output's sum is the same in
+// both: the choice changes no bit.
+//
+// In LDS a row is 64 k of one m (or n) in eight chunks of 16 bytes, chunk q at q ^
+// chunk_turn(row): a wave's reads (8 lanes: 8 rows, one q) and its stores meet each bank
+// once (twice for KT).  TA / TB: the operand is stored K x M (K x N) and turned on the
+// way in: a thread takes 4 k x 4 columns, eight byte permutes and four 8-byte stores.
+__device__ __forceinline__ int chunk_turn(int row) { return ((row >> 1) ^ (row >> 4)) & 7; }
+template <int BT, int PF, bool TA, bool TB>
+__device__ __forceinline__ void gemm_tile(const GemmArgs &g, int bl, int gx, bf16_t (&sA)[2][BT * kBK],
+                                          bf16_t (&sB)[2][BT * kBK]) {
+    static_assert((BT == 64 || BT == 128) && PF % 2 == 0, "tile sides; tiles in flight alternate two LDS buffers");
+    static_assert(BT == 64 || !(TA || TB), "256 threads turn 64 x 64 values");
+    constexpr int kPF = PF, NW = BT * BT / 1024;
+    constexpr int TI = 1, WM = 32, TJ = 1, WN = 32, NWN = BT / WN;
+    constexpr int RPP = 8 * NW, NH = BT / RPP;  // staging rows per pass, passes
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / NWN, wn = wave % NWN;
-    const int m0 = (bl / gx) * kBM, n0 = (bl % gx) * kBN;
+    const int m0 = (bl / gx) * BT, n0 = (bl % gx) * BT;
     float16_t acc[TI][TJ];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -116,49 +118,82 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_nt(GemmArgs g0, GemmArgs g1, i
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    // staging: each thread moves NH x 16 bytes of A and of B per K tile (rows
-    // lrow + RPP h, columns lk .. lk + 7)
+    // staging: each thread moves NH x 16 bytes of A and of B per K tile: rows lrow +
+    // RPP h, columns lk .. lk + 7; turned: k = tk .. tk + 3 of columns tc .. tc + 3
     const int lrow = tid >> 3, lk = (tid & 7) * 8;
-    const __amdgpu_buffer_rsrc_t ra = operand_rsrc(g.A, g.M, g.lda), rb = operand_rsrc(g.B, g.N, g.ldb);
-    unsigned oa[NH], ob[NH];  // byte offsets of this thread's rows at k = 0
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-        oa[h] = ((unsigned)(m0 + lrow + RPP * h) * (unsigned)g.lda + (unsigned)lk) * 2u;
-        ob[h] = ((unsigned)(n0 + lrow + RPP * h) * (unsigned)g.ldb + (unsigned)lk) * 2u;
-    }
+    const int tc = (tid & 15) * 4, tk = (tid >> 4) * 4;
+    const __amdgpu_buffer_rsrc_t ra = operand_rsrc(g.A, TA ? g.K : g.M, g.lda), rb = operand_rsrc(g.B, TB ? g.K : g.N, g.ldb);
     const int nk = (g.K + kBK - 1) / kBK, nkp = (nk + kPF - 1) / kPF * kPF;
     uint4 va[kPF][NH], vb[kPF][NH];
-    auto fetch = [&](int p, int kt) {
-        const bool in = kt * kBK + lk < g.K;  // K % 8 == 0: a thread's 8 columns are all in or all out
+    auto load = [&](uint4 (&v)[NH], const __amdgpu_buffer_rsrc_t &r, int r0, int ld, int kt, auto turned) {
+        if constexpr (decltype(turned)::value) {  // rows past K are past the range
+            unsigned w[8];
 #pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            va[p][h] = __builtin_bit_cast(
-                uint4, __builtin_amdgcn_raw_buffer_load_b128(ra, in ? oa[h] + (unsigned)kt * (kBK * 2) : kNoLoad, 0, 0));
-            vb[p][h] = __builtin_bit_cast(
-                uint4, __builtin_amdgcn_raw_buffer_load_b128(rb, in ? ob[h] + (unsigned)kt * (kBK * 2) : kNoLoad, 0, 0));
+            for (int j = 0; j < 4; ++j) {
+                const int k = kt * kBK + tk + j;
+                const u32x2_t u = __builtin_amdgcn_raw_buffer_load_b64(
+                    r, k < g.K ? ((unsigned)k * (unsigned)ld + (unsigned)(r0 + tc)) * 2u : kNoLoad, 0, 0);
+                w[2 * j] = u.x;
+                w[2 * j + 1] = u.y;
+            }
+            v[0] = uint4{w[0], w[1], w[2], w[3]};
+            v[1] = uint4{w[4], w[5], w[6], w[7]};
+        } else {
+            const bool in = kt * kBK + lk < g.K;  // K % 8 == 0: a thread's 8 columns are all in or all out
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                const unsigned o = ((unsigned)(r0 + lrow + RPP * h) * (unsigned)ld + (unsigned)lk) * 2u;
+                v[h] = __builtin_bit_cast(
+                    uint4, __builtin_amdgcn_raw_buffer_load_b128(r, in ? o + (unsigned)kt * (kBK * 2) : kNoLoad, 0, 0));
+            }
+        }
+    };
+    using TurnA = std::integral_constant<bool, TA>;
+    using TurnB = std::integral_constant<bool, TB>;
+    auto fetch = [&](int p, int kt) {
+        load(va[p], ra, m0, g.lda, kt, TurnA{});
+        load(vb[p], rb, n0, g.ldb, kt, TurnB{});
+    };
+    auto put = [&](bf16_t *S, const uint4 (&v)[NH], auto turned) {
+        if constexpr (decltype(turned)::value) {
+            const unsigned r[4][2] = {{v[0].x, v[0].y}, {v[0].z, v[0].w}, {v[1].x, v[1].y}, {v[1].z, v[1].w}};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned sel = j & 1 ? 0x07060302u : 0x05040100u;  // the high or the low halves of two rows
+                const int c = tc + j;
+                *(uint2 *)(S + c * kBK + (((tk >> 3) ^ chunk_turn(c)) << 3) + (tk & 7)) =
+                    uint2{__builtin_amdgcn_perm(r[1][j >> 1], r[0][j >> 1], sel),
+                          __builtin_amdgcn_perm(r[3][j >> 1], r[2][j >> 1], sel)};
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                const int r = lrow + RPP * h;
+                *(uint4 *)(S + r * kBK + (((lk >> 3) ^ chunk_turn(r)) << 3)) = v[h];
+            }
         }
     };
     auto stage = [&](int buf, int p) {
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            const int r = lrow + RPP * h;
-            *(uint4 *)(sA[buf] + r * kLdsRow + lk) = va[p][h];
-            *(uint4 *)(sB[buf] + r * kLdsRow + lk) = vb[p][h];
-        }
+        put(sA[buf], va[p], TurnA{});
+        put(sB[buf], vb[p], TurnB{});
     };
     auto multiply = [&](int buf) {
 #pragma unroll
         for (int kk = 0; kk < kBK; kk += 16) {
             // lane l supplies row (l % 32) of the 32 x 16 operand, k = kk + 8 (l / 32) .. + 7
             // (A and B alike, so each product pairs equal k)
-            const int kof = kk + 8 * (lane >> 5);
+            const int q = kk / 8 + (lane >> 5);
             bf16x8_t a[TI], b[TJ];
 #pragma unroll
-            for (int i = 0; i < TI; ++i)
-                a[i] = *(const bf16x8_t *)(sA[buf] + (wm * WM + i * 32 + (lane & 31)) * kLdsRow + kof);
+            for (int i = 0; i < TI; ++i) {
+                const int r = wm * WM + i * 32 + (lane & 31);
+                a[i] = *(const bf16x8_t *)(sA[buf] + r * kBK + ((q ^ chunk_turn(r)) << 3));
+            }
 #pragma unroll
-            for (int j = 0; j < TJ; ++j)
-                b[j] = *(const bf16x8_t *)(sB[buf] + (wn * WN + j * 32 + (lane & 31)) * kLdsRow + kof);
+            for (int j = 0; j < TJ; ++j) {
+                const int r = wn * WN + j * 32 + (lane & 31);
+                b[j] = *(const bf16x8_t *)(sB[buf] + r * kBK + ((q ^ chunk_turn(r)) << 3));
+            }
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -236,37 +271,6 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_nt(GemmArgs g0, GemmArgs g1, i
 }
 
 // out[c][r] = in[r][c] (bf16, R x C -> C x R), 32 x 32 tiles through LDS
-// (blockIdx.z picks one of two independent transposes, so a layer's two run in one launch)
-struct TrArgs {
-    const bf16_t *in;
-    int R, C, ldi;
-    bf16_t *out;
-    int ldo;
-};
-// one 32 x 32 tile (bx, by) of out = in^T; tiles past the matrix leave at once
-// (uniform over the block)
-__device__ __forceinline__ void transpose_tile(const TrArgs &a, int bx, int by) {
-    __shared__ bf16_t t[32][33];
-    const int c0 = bx * 32, r0 = by * 32;
-    if (c0 >= a.C || r0 >= a.R) return;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-    for (int y = ty; y < 32; y += 8) {
-        const int r = r0 + y, c = c0 + tx;
-        t[y][tx] = (r < a.R && c < a.C) ? a.in[(int64_t)r * a.ldi + c] : (bf16_t)0;
-    }
-    __syncthreads();
-    for (int y = ty; y < 32; y += 8) {
-        const int c = c0 + y, r = r0 + tx;
-        if (c < a.C && r < a.R) a.out[(int64_t)c * a.ldo + r] = t[tx][y];
-    }
-}
-
-// up to three independent transposes, blockIdx.z choosing (the grid covers the
-// largest)
-__global__ __launch_bounds__(256) void k_transpose(TrArgs a0, TrArgs a1, TrArgs a2) {
-    transpose_tile(blockIdx.z == 0 ? a0 : (blockIdx.z == 1 ? a1 : a2), blockIdx.x, blockIdx.y);
-}
-
 __global__ void k_f32_to_bf16(const float *__restrict__ in, bf16_t *__restrict__ out, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         out[i] = f2bf(in[i]);
@@ -300,25 +304,32 @@ __device__ __forceinline__ void colsum_block(const ColArgs &a, int bx) {
         a.db[n] = t;
     }
 }
-// What one layer of the backward pass needs before its two products, in one
-// launch: the transposes of its bf16 dZ and of its input activation (2 gx gy
-// tile blocks), the column sums of its fp32 dZ (its bias gradient) and,
-// optionally, of a second matrix (16 columns per block, at least 16 columns)
-// and of a third (one block per column)
-__global__ __launch_bounds__(256) void k_layer_prep(TrArgs t0, TrArgs t1, int gx, int gy, ColArgs c0, ColArgs c1,
-                                                    ColArgs c2) {
+template <int BT, int PF>
+__global__ __launch_bounds__(BT *BT / 16) void k_gemm_nt(GemmArgs g, int gx) {
+    __shared__ __attribute__((aligned(16))) bf16_t sA[2][BT * kBK], sB[2][BT * kBK];
+    gemm_tile<BT, PF, false, false>(g, blockIdx.x, gx, sA, sB);
+}
+
+// One layer of the backward pass in one launch, every output from what the layer
+// above left: the column sums of its fp32 dZ (its bias gradient) and, optionally, of a
+// second matrix (16 columns per block, at least 16 columns) and of a third (one block
+// per column); dW = dZ^T H (both operands stored batch-major: turned) and dZ_prev = dZ W
+// (W stored K-major: turned).  The transposed copies of dZ, H and the weights this
+// replaces took 5 launches a step, 6.4 to 6.8 us each (batch 1024).
+__global__ __launch_bounds__(256) void k_layer_bwd(GemmArgs dw, GemmArgs dx, int nw, int gxw, int gxx, ColArgs c0,
+                                                   ColArgs c1, ColArgs c2, int ncol) {
+    __shared__ __attribute__((aligned(16))) bf16_t sA[2][64 * kBK], sB[2][64 * kBK];
     int lb = blockIdx.x;
-    const int ntr = gx * gy;
-    if (lb < 2 * ntr) {
-        const int z = lb >= ntr, r = lb - z * ntr;
-        transpose_tile(z ? t1 : t0, r % gx, r / gx);
+    if (lb < ncol) {
+        const int n0 = (c0.N + 15) / 16, n1 = (c1.N + 15) / 16;
+        if (lb < n0) colsum_block<16>(c0, lb);
+        else if (lb < n0 + n1) colsum_block<16>(c1, lb - n0);
+        else colsum_block<1>(c2, lb - n0 - n1);
         return;
     }
-    lb -= 2 * ntr;
-    const int n0 = (c0.N + 15) / 16, n1 = (c1.N + 15) / 16;
-    if (lb < n0) colsum_block<16>(c0, lb);
-    else if (lb < n0 + n1) colsum_block<16>(c1, lb - n0);
-    else colsum_block<1>(c2, lb - n0 - n1);
+    lb -= ncol;
+    if (lb < nw) gemm_tile<64, 4, true, true>(dw, lb, gxw, sA, sB);
+    else gemm_tile<64, 4, false, true>(dx, lb - nw, gxx, sA, sB);
 }
 
 // ---------------------------------------------------------------- conv head
@@ -795,12 +806,11 @@ struct qw_surr {
     int bmax = 16384;  // rows per network pass (training batches, forward chunks)
     float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // fp32 params, Adam moments, grads
     bf16_t *pb = nullptr;                                          // bf16 mirror of p
-    bf16_t *W2T = nullptr, *W3T = nullptr, *W4T = nullptr;
     // activations (bmax rows)
     bf16_t *xb = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr;
     float *z4 = nullptr, *q = nullptr, *yb = nullptr, *dl = nullptr, *lrow = nullptr, *part = nullptr;
-    float *dz = nullptr;                       // fp32 dz (bmax x 1024)
-    bf16_t *dzb = nullptr, *dzb2 = nullptr, *dzT = nullptr, *hT = nullptr;  // dzb, dzb2: bf16 dZ of alternate layers
+    float *dz = nullptr, *dz2 = nullptr;       // fp32 dZ of alternate layers (bmax x 1024)
+    bf16_t *dzb = nullptr, *dzb2 = nullptr;  // bf16 dZ of alternate layers
     int32_t *idx = nullptr;
     int32_t *tb = nullptr;                     // steps of the batch rows
     int64_t adam_t = 0;
@@ -813,8 +823,8 @@ namespace {
 
 void free_surr(qw_surr *s) {
     if (!s) return;
-    void *bufs[] = {s->p, s->m, s->v, s->g, s->pb, s->W2T, s->W3T, s->W4T, s->xb, s->h1, s->h2, s->h3,
-                    s->z4, s->q, s->yb, s->dl, s->lrow, s->part, s->dz, s->dzb, s->dzb2, s->dzT, s->hT, s->idx, s->tb};
+    void *bufs[] = {s->p, s->m, s->v, s->g, s->pb, s->xb, s->h1, s->h2, s->h3,
+                    s->z4, s->q, s->yb, s->dl, s->lrow, s->part, s->dz, s->dz2, s->dzb, s->dzb2, s->idx, s->tb};
     for (void *b : bufs) (void)hipFree(b);
     for (WorkBuf *w : {&s->w_xb, &s->w_t32, &s->w_out, &s->w_n, &s->w_t, &s->w_a, &s->w_p, &s->w_idx, &s->w_plain, &s->w_net,
                        &s->w_tv})
@@ -825,82 +835,56 @@ void free_surr(qw_surr *s) {
     delete s;
 }
 
+// (ta, tb: A is stored K x M, B is stored K x N)
 hipError_t gemm_args(GemmArgs &a, const bf16_t *A, int lda, const bf16_t *B, int ldb, int M, int N, int K, float alpha,
-                     const float *bias, const bf16_t *mask, int ldm, int relu, float *C, int ldc, bf16_t *Cb, int ldcb) {
+                     const float *bias, const bf16_t *mask, int ldm, int relu, float *C, int ldc, bf16_t *Cb, int ldcb,
+                     bool ta = false, bool tb = false) {
     if (K % kKAlign) return hipErrorInvalidValue;
     // the mask is read as the aligned 4 bytes holding each element: with an even
     // row stride the last element's 4 bytes lie inside the matrix
     if (mask && (ldm & 1)) return hipErrorInvalidValue;
     // operand byte offsets (padded rows included) fit the descriptors' 31 bits
-    if ((int64_t)(M + kBM) * lda * 2 >= (int64_t)kNoLoad || (int64_t)(N + kBN) * ldb * 2 >= (int64_t)kNoLoad ||
+    if ((int64_t)((ta ? K : M) + kBM) * lda * 2 >= (int64_t)kNoLoad ||
+        (int64_t)((tb ? K : N) + kBM) * ldb * 2 >= (int64_t)kNoLoad ||
         (int64_t)(M + kBM) * ldm * 2 >= (int64_t)kNoLoad || (int64_t)(M + kBM) * ldc * 4 >= (int64_t)kNoLoad ||
         (int64_t)(M + kBM) * ldcb * 2 >= (int64_t)kNoLoad)
         return hipErrorInvalidValue;
     a = GemmArgs{A, lda, B, ldb, M, N, K, alpha, bias, mask, ldm, relu, C, ldc, Cb, ldcb};
     return hipSuccess;
 }
-inline int gemm_gx(const GemmArgs &a) { return (a.N + kBN - 1) / kBN; }
-inline int gemm_blocks(const GemmArgs &a) { return gemm_gx(a) * ((a.M + kBM - 1) / kBM); }
+inline int gemm_gx(const GemmArgs &a, int bt) { return (a.N + bt - 1) / bt; }
+inline int gemm_blocks(const GemmArgs &a, int bt) { return gemm_gx(a, bt) * ((a.M + bt - 1) / bt); }
 
-// a launch of nb blocks (na of them the first product)
-void launch_gemm(hipStream_t st, int nb, const GemmArgs &a, const GemmArgs &b, int na) {
-    hipLaunchKernelGGL(k_gemm_nt<16>, dim3(nb), dim3(1024), 0, st, a, b, na, gemm_gx(a), gemm_gx(b));
-}
-
+// Tiles of 64 where those of 128 leave compute units idle: a 1024 x 1024 x 1024 product
+// (64 tiles of 128) 13 -> 10 us; with 256 tiles of 128 they run 10 % longer, with 1024 25 %.
+constexpr int kFullTiles = 256;
 hipError_t gemm(hipStream_t st, const bf16_t *A, int lda, const bf16_t *B, int ldb, int M, int N, int K, float alpha,
                 const float *bias, const bf16_t *mask, int ldm, int relu, float *C, int ldc, bf16_t *Cb, int ldcb) {
     GemmArgs a;
     hipError_t e = gemm_args(a, A, lda, B, ldb, M, N, K, alpha, bias, mask, ldm, relu, C, ldc, Cb, ldcb);
     if (e != hipSuccess) return e;
-    const int nb = gemm_blocks(a);
-    launch_gemm(st, nb, a, a, nb);
+    if (gemm_blocks(a, 128) < kFullTiles)
+        hipLaunchKernelGGL((k_gemm_nt<64, 4>), dim3(gemm_blocks(a, 64)), dim3(256), 0, st, a, gemm_gx(a, 64));
+    else
+        hipLaunchKernelGGL((k_gemm_nt<128, 2>), dim3(gemm_blocks(a, 128)), dim3(1024), 0, st, a, gemm_gx(a, 128));
     return hipGetLastError();
 }
 
-// two independent products in one launch
-hipError_t gemm_pair(hipStream_t st, const GemmArgs &a, const GemmArgs &b) {
-    const int na = gemm_blocks(a), nb = gemm_blocks(b);
-    launch_gemm(st, na + nb, a, b, na);
-    return hipGetLastError();
-}
-
-// n (1 to 3) independent transposes in one launch
-hipError_t transposes(hipStream_t st, const TrArgs *a, int n) {
-    int mc = 0, mr = 0;
-    for (int i = 0; i < n; ++i) {
-        mc = std::max(mc, a[i].C);
-        mr = std::max(mr, a[i].R);
-    }
-    const dim3 grid((mc + 31) / 32, (mr + 31) / 32, n);
-    hipLaunchKernelGGL(k_transpose, grid, dim3(256), 0, st, a[0], a[n > 1 ? 1 : 0], a[n > 2 ? 2 : 0]);
-    return hipGetLastError();
-}
-
-// one backward layer's transposes and column sums (k_layer_prep); c1.N, c2.N = 0:
-// none
-hipError_t layer_prep(hipStream_t st, const TrArgs &t0, const TrArgs &t1, const ColArgs &c0, const ColArgs &c1,
-                      const ColArgs &c2) {
+// one layer of the backward pass (dx.M = 0: no input gradient; c1.N, c2.N = 0: none)
+hipError_t layer_bwd(hipStream_t st, const GemmArgs &dw, const GemmArgs &dx, const ColArgs &c0, const ColArgs &c1,
+                     const ColArgs &c2) {
     if (c0.N < 16 || (c1.N != 0 && c1.N < 16) || c2.N < 0) return hipErrorInvalidValue;
-    const int gx = (std::max(t0.C, t1.C) + 31) / 32, gy = (std::max(t0.R, t1.R) + 31) / 32;
-    const int blocks = 2 * gx * gy + (c0.N + 15) / 16 + (c1.N + 15) / 16 + c2.N;
-    hipLaunchKernelGGL(k_layer_prep, dim3(blocks), dim3(256), 0, st, t0, t1, gx, gy, c0, c1, c2);
+    const int nw = gemm_blocks(dw, 64), nx = gemm_blocks(dx, 64);
+    const int ncol = (c0.N + 15) / 16 + (c1.N + 15) / 16 + c2.N;
+    hipLaunchKernelGGL(k_layer_bwd, dim3(ncol + nw + nx), dim3(256), 0, st, dw, dx, nw, gemm_gx(dw, 64), gemm_gx(dx, 64),
+                       c0, c1, c2, ncol);
     return hipGetLastError();
 }
 
-// the transposed bf16 weights the input-gradient products read
-hipError_t weight_transposes(qw_surr *s) {
-    const TrArgs t[3] = {TrArgs{s->pb + L.W2, kH2, kH1, kH1, s->W2T, kH2},
-                         TrArgs{s->pb + L.W3, kH3, kH2, kH2, s->W3T, kH3},
-                         TrArgs{s->pb + L.W4, kZ4, kH3, kH3, s->W4T, kZ4}};
-    return transposes(s->stream, t, 3);
-}
-
-// refresh the bf16 mirror (from p) and the transposed weights
+// refresh the bf16 mirror (from p)
 hipError_t refresh_weights(qw_surr *s) {
     hipLaunchKernelGGL(k_f32_to_bf16, dim3(2048), dim3(256), 0, s->stream, (const float *)s->p, s->pb, L.total);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = weight_transposes(s);
-    return e;
+    return hipGetLastError();
 }
 
 // forward of B rows already in s->xb; y (device, B x 512) optional -> dl, lrow
@@ -979,32 +963,32 @@ hipError_t backward(qw_surr *s, int B, float *loss_sum = nullptr) {
         const bf16_t *hin;  // layer input activation (B x kin)
         int kin, kout;
         int64_t W, b;
-        const bf16_t *WT;   // kin x kout (transposed weight) for dX; null for the first layer
     } lays[4] = {
-        {s->xb, kF, kH1, L.W1, L.b1, nullptr},
-        {s->h1, kH1, kH2, L.W2, L.b2, s->W2T},
-        {s->h2, kH2, kH3, L.W3, L.b3, s->W3T},
-        {s->h3, kH3, kZ4, L.W4, L.b4, s->W4T},
+        {s->xb, kF, kH1, L.W1, L.b1},
+        {s->h1, kH1, kH2, L.W2, L.b2},
+        {s->h2, kH2, kH3, L.W3, L.b3},
+        {s->h3, kH3, kZ4, L.W4, L.b4},
     };
     for (int li = 3; li >= 0; --li) {
         const Lay &ly = lays[li];
-        // s->dz holds dZ of this layer (fp32, B x kout) and dzb its bf16 copy: made
-        // by the head's backward for the top layer, else by the product below
-        bf16_t *dzb = (li & 1) ? s->dzb : s->dzb2, *dzb_next = (li & 1) ? s->dzb2 : s->dzb;
-        e = layer_prep(st, TrArgs{dzb, B, ly.kout, ly.kout, s->dzT, B}, TrArgs{ly.hin, B, ly.kin, ly.kin, s->hT, B},
-                       ColArgs{s->dz, B, ly.kout, s->g + ly.b},
-                       li == 3 ? ColArgs{s->part, B, 19, s->g + L.cw} : ColArgs{nullptr, 0, 0, nullptr},
-                       li == 3 && loss_sum ? ColArgs{s->lrow, B, 1, loss_sum} : ColArgs{nullptr, 0, 0, nullptr});
+        // dz and dzb hold dZ of this layer (fp32, B x kout) and its bf16 copy: made by
+        // the head's backward for the top layer, else by the layer above, which reads
+        // the other two
+        const bool odd = (li & 1) != 0;
+        const float *dz = odd ? s->dz : s->dz2;
+        const bf16_t *dzb = odd ? s->dzb : s->dzb2;
         // dW[n][k] = sum_b dZ[b][n] Hin[b][k], and (below the first layer) dZ_prev = (dZ W)
-        // masked by the previous activation > 0: independent products, one launch
-        GemmArgs dw, dx;
-        if (e == hipSuccess)
-            e = gemm_args(dw, s->dzT, B, s->hT, B, ly.kout, ly.kin, B, 1.0f, nullptr, nullptr, 0, 0, s->g + ly.W, ly.kin,
-                          nullptr, 0);
+        // masked by the previous activation > 0
+        GemmArgs dw, dx{};
+        e = gemm_args(dw, dzb, ly.kout, ly.hin, ly.kin, ly.kout, ly.kin, B, 1.0f, nullptr, nullptr, 0, 0, s->g + ly.W,
+                      ly.kin, nullptr, 0, true, true);
         if (e == hipSuccess && li > 0)
-            e = gemm_args(dx, dzb, ly.kout, ly.WT, ly.kout, B, ly.kin, ly.kout, 1.0f, nullptr, ly.hin, ly.kin, 0, s->dz,
-                          ly.kin, dzb_next, ly.kin);
-        if (e == hipSuccess) e = li > 0 ? gemm_pair(st, dw, dx) : gemm_pair(st, dw, GemmArgs{});
+            e = gemm_args(dx, dzb, ly.kout, s->pb + ly.W, ly.kin, B, ly.kin, ly.kout, 1.0f, nullptr, ly.hin, ly.kin, 0,
+                          odd ? s->dz2 : s->dz, ly.kin, odd ? s->dzb2 : s->dzb, ly.kin, false, true);
+        if (e == hipSuccess)
+            e = layer_bwd(st, dw, dx, ColArgs{dz, B, ly.kout, s->g + ly.b},
+                          li == 3 ? ColArgs{s->part, B, 19, s->g + L.cw} : ColArgs{nullptr, 0, 0, nullptr},
+                          li == 3 && loss_sum ? ColArgs{s->lrow, B, 1, loss_sum} : ColArgs{nullptr, 0, 0, nullptr});
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1018,9 +1002,7 @@ hipError_t adam_step(qw_surr *s, float lr, float wd, const GatherArgs &next) {
     constexpr int na = 2048;
     hipLaunchKernelGGL(k_adam, dim3(na + std::max(next.B, 0)), dim3(256), 0, s->stream, s->p, s->m, s->v,
                        (const float *)s->g, s->pb, L.total, lr, b1, b2, eps, c1, c2, wd, na, next);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = weight_transposes(s);
-    return e;
+    return hipGetLastError();
 }
 
 int alloc_surr(qw_surr *s) {
@@ -1032,8 +1014,6 @@ int alloc_surr(qw_surr *s) {
         {(void **)&s->p, sizeof(float) * L.total}, {(void **)&s->m, sizeof(float) * L.total},
         {(void **)&s->v, sizeof(float) * L.total}, {(void **)&s->g, sizeof(float) * L.total},
         {(void **)&s->pb, sizeof(bf16_t) * L.total},
-        {(void **)&s->W2T, sizeof(bf16_t) * kH2 * kH1}, {(void **)&s->W3T, sizeof(bf16_t) * kH3 * kH2},
-        {(void **)&s->W4T, sizeof(bf16_t) * kZ4 * kH3},
         {(void **)&s->xb, sizeof(bf16_t) * B * kF}, {(void **)&s->h1, sizeof(bf16_t) * B * kH1},
         {(void **)&s->h2, sizeof(bf16_t) * B * kH2}, {(void **)&s->h3, sizeof(bf16_t) * B * kH3},
         {(void **)&s->z4, sizeof(float) * B * kZ4}, {(void **)&s->q, sizeof(float) * B * kBins},
@@ -1041,7 +1021,7 @@ int alloc_surr(qw_surr *s) {
         {(void **)&s->lrow, sizeof(float) * B}, {(void **)&s->part, sizeof(float) * B * 19},
         {(void **)&s->dz, sizeof(float) * B * 1024}, {(void **)&s->dzb, sizeof(bf16_t) * B * 1024},
         {(void **)&s->dzb2, sizeof(bf16_t) * B * 1024},
-        {(void **)&s->dzT, sizeof(bf16_t) * B * 1024}, {(void **)&s->hT, sizeof(bf16_t) * B * 1024},
+        {(void **)&s->dz2, sizeof(float) * B * 1024},
         {(void **)&s->idx, sizeof(int32_t) * B}, {(void **)&s->tb, sizeof(int32_t) * B},
     };
     for (auto &a : list) {
