@@ -395,6 +395,13 @@ __device__ __forceinline__ float block_max(float v, float *red4) {
     return r;
 }
 
+// the LDS stores of a wave's lanes before this are seen by its loads after it
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // sum_j q_j ov_j over the cells overlapping [u0, u1) (units of 1 / kCells site;
 // cell j is [j ns, (j + 1) ns)), the overlaps exact integers
 __device__ __forceinline__ double cell_overlap_sum(const float *sq, int u0, int u1, int ns, float rns) {
@@ -404,16 +411,82 @@ __device__ __forceinline__ double cell_overlap_sum(const float *sq, int u0, int 
     j -= j * ns > u0;
     j += (j + 1) * ns <= u0;
     double acc = 0.0;
-    for (; j < kCells && j * ns < u1; ++j) {
-        const int ov = min((j + 1) * ns, u1) - max(j * ns, u0);
-        acc += (double)sq[j] * (double)ov;
-    }
+    // (u1 <= kCells ns: the last cell ends the loop too)
+    for (int c = j * ns; c < u1; ++j, c += ns) acc += (double)sq[j] * (double)(min(c + ns, u1) - max(c, u0));
     return acc;
 }
 
-// TRAIN: with targets y (loss and dl; the site gradients need a site array),
-// else the prediction pass only
-template <bool TRAIN>
+// sums of bins: p = R(T) q.  The sites of a bin (offsets dx = 2k - T in its range, of
+// the parity of T) are a run k = ka..kb, i.e. [kCells ka, kCells (kb + 1)) in
+// units of 1 / kCells site, so p = sum_j q_j ov_j / ns over the cells the run
+// overlaps; the start site (dx = 0, T even) gives half its mass to each middle bin
+__device__ __forceinline__ float bin_mass(const float *sq, int bin, int w, int T, float rns, double inv_ns) {
+    const int hb = kBins / 2, ns = T + 1;
+    const int lo = bin < hb ? -(hb - bin) * w : (bin - hb) * w + 1;
+    const int hi = bin < hb ? -(hb - bin - 1) * w - 1 : (bin - hb + 1) * w;
+    const int ka = max((T + lo + 1) >> 1, 0), kb = min((T + hi) >> 1, T);  // ceil, floor
+    double acc = ka <= kb ? cell_overlap_sum(sq, kCells * ka, kCells * (kb + 1), ns, rns) : 0.0;
+    if ((bin == hb - 1 || bin == hb) && (T & 1) == 0)
+        acc += 0.5 * cell_overlap_sum(sq, kCells * (T / 2), kCells * (T / 2 + 1), ns, rns);
+    return (float)(acc * inv_ns);
+}
+
+// The prediction's head: a wave per row, eight positions a lane (i = lane + 64 m, so the
+// sums pair up as k_head_fwd's do: the same bits), no barrier.  A block per row with its
+// six barriers took 38.6 us for 15000 rows (92 MB), now 31: the cells
+// of each bin, one after the other, set the pace.
+__global__ __launch_bounds__(256) void k_head_rows(const float *__restrict__ z4, const float *__restrict__ cw,
+                                                   const float *__restrict__ cb, const int32_t *__restrict__ Tst, int w,
+                                                   float *__restrict__ pout, int rows) {
+    __shared__ __attribute__((aligned(16))) float mem[4][2][kBins + 2 * kPad];
+    static_assert(kPad == 4 && kBins == 512 && kCells == kBins, "float4 rows; eight positions a lane");
+    const int lane = threadIdx.x & 63, b = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (b >= rows) return;
+    float(*sz)[kBins + 2 * kPad] = mem[threadIdx.x >> 6];
+    const float4 *zr = (const float4 *)(z4 + (int64_t)b * kZ4);
+    if (lane < 2 * kPad) {
+        const int i = lane < kPad ? lane : kBins + lane;
+        sz[0][i] = 0.0f;
+        sz[1][i] = 0.0f;
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) *(float4 *)&sz[c][kPad + 4 * (lane + 64 * k)] = zr[128 * c + 64 * k + lane];
+    wave_lds_order();
+    float l[8], mx = -INFINITY;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        float v = cb[0];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int j = 0; j < kTaps; ++j) v += cw[c * kTaps + j] * sz[c][lane + 64 * m + j];
+        l[m] = v;
+        mx = fmaxf(mx, v);
+    }
+    mx = wave_max(mx);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) l[m] = expf(l[m] - mx);
+    float part[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) part[m] = wave_sum(l[m] + l[m + 4]);
+    const float den = ((part[0] + part[1]) + part[2]) + part[3];
+    float *sq = sz[0];
+    wave_lds_order();  // every position read
+#pragma unroll
+    for (int m = 0; m < 8; ++m) sq[lane + 64 * m] = l[m] / den;
+    wave_lds_order();
+    int T = Tst[b];
+    T = T < 0 ? 0 : (T > kMaxSites - 1 ? kMaxSites - 1 : T);
+    const double inv_ns = 1.0 / (double)(T + 1);
+    const float rns = 1.0f / (float)(T + 1);
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        pout[(int64_t)b * kBins + lane + 64 * m] = bin_mass(sq, lane + 64 * m, w, T, rns, inv_ns);
+}
+
+// the training head: also the loss against y and dl
 __global__ __launch_bounds__(256) void k_head_fwd(const float *__restrict__ z4, const float *__restrict__ cw,
                                                   const float *__restrict__ cb, const int32_t *__restrict__ Tst,
                                                   int w, float *__restrict__ pout, const float *__restrict__ y,
@@ -421,8 +494,8 @@ __global__ __launch_bounds__(256) void k_head_fwd(const float *__restrict__ z4, 
     __shared__ float sz[2][kBins + 2 * kPad];
     __shared__ float red4[4];
     __shared__ float sq[kCells];
-    __shared__ float sm[TRAIN ? kMaxSites : 1];  // site gradients
-    __shared__ float sg[TRAIN ? kBins : 1];      // bin gradients
+    __shared__ float sm[kMaxSites];  // site gradients
+    __shared__ float sg[kBins];      // bin gradients
     const int b = blockIdx.x, t = threadIdx.x;
     const float *zr = z4 + (int64_t)b * kZ4;
     for (int i = t; i < kBins + 2 * kPad; i += 256) {
@@ -456,26 +529,13 @@ __global__ __launch_bounds__(256) void k_head_fwd(const float *__restrict__ z4, 
     const double inv_ns = 1.0 / (double)ns;
     const float rns = 1.0f / (float)ns;
     __syncthreads();
-    // bins: p = R(T) q.  The sites of bin b (offsets dx = 2k - T in its range, of
-    // the parity of T) are a run k = ka..kb, i.e. [kCells ka, kCells (kb + 1)) in
-    // units of 1 / kCells site, so p_b = sum_j q_j ov_j / ns over the cells the run
-    // overlaps; the start site (dx = 0, T even) gives half its mass to each middle bin
-    const int hb = kBins / 2;
     float pb[2];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
         const int bin = t + 256 * hh;
-        const int lo = bin < hb ? -(hb - bin) * w : (bin - hb) * w + 1;
-        const int hi = bin < hb ? -(hb - bin - 1) * w - 1 : (bin - hb + 1) * w;
-        const int ka = max((T + lo + 1) >> 1, 0), kb = min((T + hi) >> 1, T);  // ceil, floor
-        double acc = ka <= kb ? cell_overlap_sum(sq, kCells * ka, kCells * (kb + 1), ns, rns) : 0.0;
-        if ((bin == hb - 1 || bin == hb) && (T & 1) == 0)
-            acc += 0.5 * cell_overlap_sum(sq, kCells * (T / 2), kCells * (T / 2 + 1), ns, rns);
-        const float v = (float)(acc * inv_ns);
-        pb[hh] = v;
-        if (pout) pout[(int64_t)b * kBins + bin] = v;
+        pb[hh] = bin_mass(sq, bin, w, T, rns, inv_ns);
+        if (pout) pout[(int64_t)b * kBins + bin] = pb[hh];
     }
-    if constexpr (!TRAIN) return;
     const float y0 = y[(int64_t)b * kBins + t], y1 = y[(int64_t)b * kBins + t + 256];
     float lv = 0.0f;
     if (y0 > 0.0f) lv += y0 * (logf(y0) - logf(fmaxf(pb[0], 1e-30f)));
@@ -907,13 +967,13 @@ hipError_t forward(qw_surr *s, int B, int Bscale, const float *y, const bf16_t *
     if (e != hipSuccess) return e;
     const int w = (int)(((s->train_n - 1) / 2) / (kBins / 2));
     if (y)
-        hipLaunchKernelGGL(k_head_fwd<true>, dim3(B), dim3(256), 0, st, (const float *)s->z4,
+        hipLaunchKernelGGL(k_head_fwd, dim3(B), dim3(256), 0, st, (const float *)s->z4,
                            (const float *)(s->p + L.cw), (const float *)(s->p + L.cb), tin, w < 1 ? 1 : w, qout, y,
                            s->dl, s->lrow, Bscale);
     else
-        hipLaunchKernelGGL(k_head_fwd<false>, dim3(rows >= 0 ? rows : B), dim3(256), 0, st, (const float *)s->z4,
+        hipLaunchKernelGGL(k_head_rows, dim3(((rows >= 0 ? rows : B) + 3) / 4), dim3(256), 0, st, (const float *)s->z4,
                            (const float *)(s->p + L.cw), (const float *)(s->p + L.cb), tin, w < 1 ? 1 : w, qout,
-                           nullptr, nullptr, nullptr, Bscale);
+                           rows >= 0 ? rows : B);
     return hipGetLastError();
 }
 

@@ -44,8 +44,10 @@ def test_gradients_of_turned_operands(n):
     activation that rounds the other way is 2^-9 off, and few do: the bound is 1e-2
     of the gradient's norm."""
     N, T, ang, psi0 = _walk_params(n, n)
-    rng = np.random.default_rng(n)
-    y = rng.random((n, 512))
+    b = qwalk.Batch(N, T, ang, psi0, prec=qwalk.QW_C64, nbins=512)  # (targets with no mass out of the walk's reach:
+    b.run()                                                         # the loss is infinite there)
+    y = b.binned().astype(np.float64)
+    b.destroy()
     y /= y.sum(axis=1, keepdims=True)
     s = qwalk.Surrogate(seed=n)
     X = s.features(N, T, ang, psi0)
