@@ -307,7 +307,11 @@ __device__ __forceinline__ void colsum_block(const ColArgs &a, int bx) {
 template <int BT, int PF>
 __global__ __launch_bounds__(BT *BT / 16) void k_gemm_nt(GemmArgs g, int gx) {
     __shared__ __attribute__((aligned(16))) bf16_t sA[2][BT * kBK], sB[2][BT * kBK];
-    gemm_tile<BT, PF, false, false>(g, blockIdx.x, gx, sA, sB);
+    // the hardware deals blocks to the 8 XCDs in turn: each XCD takes a contiguous range
+    // of tiles, whole rows of tiles, so A comes to one L2 and not to all (a bijection): prediction of
+    // 60001 walks 1.33 -> 1.25 ms
+    const int nb = gridDim.x, xcd = blockIdx.x & 7, i = blockIdx.x >> 3, per = nb >> 3, rem = nb & 7;
+    gemm_tile<BT, PF, false, false>(g, (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + i, gx, sA, sB);
 }
 
 // One layer of the backward pass in one launch, every output from what the layer
