@@ -488,12 +488,13 @@ def traffic_from_profile(kernel_sha: str, name: str = "grover4096_c128"):
 
 def kernel_source_sha():
     """sha256 of what sets the torus walk's launches: the streaming kernels'
-    source (qw_stream_wg.hip and the regions of qw_kernels.hip between the
-    begin / end markers, device code and launchers) and the choice of launches
-    (the marked regions of qw_api.hip)."""
+    source (qw_cone.hip, qw_stream_wg.hip and the regions of qw_kernels.hip
+    between the begin / end markers, device code and launchers) and the choice
+    of launches (the marked regions of qw_api.hip)."""
     h = hashlib.sha256()
-    with open(os.path.join(ROOT, "paper_1003_3779_amd", "csrc", "qw_stream_wg.hip"), "rb") as f:
-        h.update(f.read())
+    for fname in ("qw_cone.hip", "qw_stream_wg.hip"):
+        with open(os.path.join(ROOT, "paper_1003_3779_amd", "csrc", fname), "rb") as f:
+            h.update(f.read())
     for fname, tag in (("qw_kernels.hip", b"torus streaming kernel"), ("qw_api.hip", b"torus launch choice")):
         with open(os.path.join(ROOT, "paper_1003_3779_amd", "csrc", fname), "rb") as f:
             src = f.read()

@@ -144,7 +144,7 @@ enum {
     QW_KERNEL_STEP = 0,        /* one step per launch, one thread per site */
     QW_KERNEL_RING_WHOLE = 1,  /* a whole ring in one workgroup, many steps per launch */
     QW_KERNEL_RING_TILES = 2,  /* ring in wave-sized register tiles, K steps per launch */
-    QW_KERNEL_STREAM2D = 3,    /* torus, row-streaming register kernel, K steps per launch */
+    QW_KERNEL_STREAM2D = 3,    /* torus, K steps per launch, on the lattice or the live sites */
     QW_KERNEL_KINDS = 4
 };
 
@@ -321,8 +321,10 @@ int walk_run_noalloc(const qw_lattice *lattice, const qw_coin *coin, const doubl
  * (-N/2, N/2]), optionally nbins symmetric bins of P (offsets -k*w..-(k-1)*w-1
  * to bin h-k, (k-1)*w+1..k*w to bin h+k-1, the start site half to bins h-1
  * and h; h = nbins/2, w = floor((N-1)/2 / h)) and optionally every full P(x).
- * Walks run longest-first from an atomic queue; a run is one replay of a
- * captured hipGraph (queue reset + the persistent kernel).  With stream NULL
+ * Short walks whose cone does not meet itself run in registers, long ones together,
+ * a block of steps per launch, walks with links or walls a workgroup each, the rest
+ * (and forced variants) longest-first from an atomic queue; a run is one replay of a
+ * captured hipGraph of these kernels.  With stream NULL
  * the batch uses a private stream and calls return only when done.
  * ------------------------------------------------------------------------ */
 typedef struct qw_batch *qw_batch_t;

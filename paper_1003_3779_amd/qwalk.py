@@ -441,7 +441,7 @@ def _bcheck(rc: int):
 
 
 class Batch:
-    """Independent ring walks in one persistent launch (walk_batch_*).  The options
+    """Independent ring walks, one graph replay per run (walk_batch_*).  The options
     are those of qw_batch_opts; full_lattice=True makes the tiled rings update both
     parities of their light cone (by default a ring whose cone never wraps keeps
     only the live parity: the same results, half the work)."""
