@@ -1096,6 +1096,7 @@ BatchArgs make_args(qw_batch *b, const WalkDesc *walks, const int32_t *order, in
 // over the rest (if any); grid: the general kernel's workgroups
 hipError_t enqueue(qw_batch *b, const BatchArgs &A, int grid) {
     if (A.n < 1) return hipSuccess;
+    if (A.n_slim > 0 && !A.slim_slots) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(1), 0, b->stream, b->d_queue);
     if (A.n_slim > 0) {
         const int gs = std::max(1, std::min(b->grid_slim, (int)A.n_slim));
@@ -1321,6 +1322,19 @@ hipError_t upload_long(qw_batch *b) {
     return e;
 }
 
+// the slim kernel's slot buffers, where the order (build_order) gives it walks: after
+// create, and after tuning, which may pick its tiles for walks that had others
+hipError_t alloc_slim(qw_batch *b) {
+    if (b->n_slim == 0 || b->d_slim_slots) return hipSuccess;
+    const hipError_t e =
+        hipMalloc(&b->d_slim_slots, (size_t)b->grid_slim * 4 * kSlimSlots * (b->prec == QW_C128 ? 16 : 8));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        b->d_slim_slots = nullptr;
+    }
+    return e;
+}
+
 // the largest ring the queue runs through the slot buffers
 int64_t queue_sites(const qw_batch *b, bool every) {
     int64_t m = 0;
@@ -1529,7 +1543,7 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
     };
     bool ok = alloc((void **)&b->d_walks, sizeof(WalkDesc) * n) && alloc((void **)&b->d_order, sizeof(int32_t) * n) &&
               alloc((void **)&b->d_queue, 256) && alloc(&b->d_slots, (size_t)b->grid * 4 * b->slot_elems * esz) &&
-              alloc(&b->d_slim_slots, b->n_slim > 0 ? (size_t)b->grid_slim * 4 * kSlimSlots * esz : 0) &&
+              (e = alloc_slim(b)) == hipSuccess &&
               alloc((void **)&b->d_moments, sizeof(double) * 3 * n) &&
               (b->nbins == 0 || alloc((void **)&b->d_bins, sizeof(float) * b->nbins * n)) &&
               (!b->keep || alloc((void **)&b->d_P, sizeof(double) * off));
@@ -1675,6 +1689,9 @@ int walk_batch_tune(qw_batch_t b, int32_t samples, int32_t save) {
     }
     // per bucket: the tiled walks of the bucket, a spread sample by work
     std::vector<int32_t> bucket_walks[3];
+    std::vector<int32_t> old_cfg(b->n);
+    const int old_bucket[3] = {b->bucket_cfg[0], b->bucket_cfg[1], b->bucket_cfg[2]};
+    for (int64_t i = 0; i < b->n; ++i) old_cfg[i] = b->walks[i].cfg;
     for (int64_t i = 0; i < b->n; ++i)
         if (b->walks[i].cfg >= 0) bucket_walks[size_bucket(b->walks[i].N)].push_back((int32_t)i);
     for (int bk = 0; bk < 3; ++bk) {
@@ -1745,6 +1762,12 @@ int walk_batch_tune(qw_batch_t b, int32_t samples, int32_t save) {
     // old part sizes)
     slots.restore();
     build_order(b);
+    if (alloc_slim(b) != hipSuccess) {  // the batch stays as it was
+        for (int64_t i = 0; i < b->n; ++i) b->walks[i].cfg = old_cfg[i];
+        for (int bk = 0; bk < 3; ++bk) b->bucket_cfg[bk] = old_bucket[bk];
+        build_order(b);
+        return bfail(QW_ENOMEM, "hipMalloc of the slot buffers failed");
+    }
     QB_HIP(upload_long(b), "the long walks' plan");
     QB_HIP(hipMemcpyAsync(b->d_walks, b->walks.data(), sizeof(WalkDesc) * b->n, hipMemcpyHostToDevice, b->stream),
            "upload of the walk table");
