@@ -376,7 +376,8 @@ typedef struct {
     double est_updates;        /* site*coin updates one run performs (light cone, or its live
                                   half on the live sublattice; whole rings in full) */
     double last_run_ms;        /* HIP-event time of the latest walk_batch_run */
-    int32_t bucket_cfg[3];     /* tiled variant (0..3) per size bucket N <= 1e4, <= 1e5, larger */
+    int32_t bucket_cfg[3];     /* tiled variant (0..7) of the walks in the queue per size bucket
+                                  N <= 1e4, <= 1e5, larger */
     int32_t bucket_tile_sites[3];
     int32_t bucket_depth[3];
     int32_t reserved;
@@ -406,8 +407,9 @@ int walk_batch_binned(qw_batch_t b, float *out, int32_t out_on_device);
 int walk_batch_probabilities(qw_batch_t b, double *out, int64_t *offsets, int32_t out_on_device);
 int walk_batch_info(qw_batch_t b, qw_batch_info *out);
 /* Autotuner: per size bucket, time every tiled variant (one run each, after
- * one warm-up run) on `samples` walks of the bucket (spread over their work,
- * the heaviest included: its time bounds the run's) and keep the fastest;
+ * one warm-up run) on `samples` walks that the queue runs (spread over their work,
+ * the heaviest included: its time bounds the run's) and keep the fastest; walks on
+ * the sites they can reach have no variant and are left alone;
  * synchronises; on a bucket of rings near 1e6 sites this takes minutes.  save != 0 writes
  * the choice to the tuning cache ($QWALK_TUNE_CACHE, else
  * ~/.cache/qwalk_tune.txt), read by later walk_batch_create calls on the same

@@ -925,6 +925,11 @@ int size_bucket(int64_t N) {
     if (N <= 100000) return 1;
     return 2;
 }
+// untuned default per size bucket (N <= 1e4, <= 1e5, larger): (128 slots, 32
+// steps) for the short rings, whose cones span few tiles (on the live
+// sublattice 65536 rings of 4097 sites: 29.4 ms against 31.9 with 256 slots),
+// (1024, 64) for the long ones
+constexpr int kDefaultCfg[3] = {7, 3, 3};
 
 std::string tune_cache_path() {
     const char *p = getenv("QWALK_TUNE_CACHE");
@@ -1029,11 +1034,7 @@ struct qw_batch {
     void *d_slim_slots = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
-    // untuned default per size bucket (N <= 1e4, <= 1e5, larger): (128 slots, 32
-    // steps) for the short rings, whose cones span few tiles (on the live
-    // sublattice 65536 rings of 4097 sites: 29.4 ms against 31.9 with 256 slots),
-    // (1024, 64) for the long ones
-    int bucket_cfg[3] = {7, 3, 3};
+    int bucket_cfg[3];  // tiled variant of the queue's walks per size bucket
     double last_ms = 0.0;
     hipEvent_t ev[2] = {nullptr, nullptr};
     bool own_stream = false;
@@ -1229,10 +1230,9 @@ bool walk_sub(const qw_batch *b, const WalkDesc &w) {
 // the updates the kernel performs: on the live sublattice half of the cone's
 // (at step t, t + 2 of its 2t + 3 offsets are live: counting half is low by at
 // most one site per step)
-bool walk_wave(const qw_batch *b, const WalkDesc &w);
-bool walk_long(const qw_batch *b, const WalkDesc &w);
+bool on_points(const qw_batch *b, const WalkDesc &w);
 double walk_performed(const qw_batch *b, const WalkDesc &w) {
-    return walk_wave(b, w) || walk_long(b, w) || walk_sub(b, w) ? 0.5 * walk_work(w) : walk_work(w);
+    return on_points(b, w) || walk_sub(b, w) ? 0.5 * walk_work(w) : walk_work(w);
 }
 
 // whether the slim kernel runs the walk: on its live sublattice with 128-slot tiles,
@@ -1251,6 +1251,17 @@ bool walk_long(const qw_batch *b, const WalkDesc &w) {
     return b->points && w.cfg >= 0 && w.rot && !b->full_lattice && w.T > 0 && !walk_wave(b, w);
 }
 
+bool on_points(const qw_batch *b, const WalkDesc &w) { return walk_wave(b, w) || walk_long(b, w); }
+
+// Variants of the tiled walks: the tuned (or forced) one of their size for those the queue
+// runs.  Walks on their live points have no tiles to choose and keep the size's default,
+// whose block depth says where their norms are checked: what the tuner found for another
+// kernel changes neither their steps per launch nor their values.
+void assign_variants(qw_batch *b) {
+    for (auto &w : b->walks)
+        if (w.cfg >= 0) w.cfg = (on_points(b, w) ? kDefaultCfg : b->bucket_cfg)[size_bucket(w.N)];
+}
+
 // the order: walks on their live points (in registers, then the long ones by block
 // depth), then the queue: the slim kernel's walks, the other tiled walks, the walks held
 // whole; each part longest-first.  Sets the parts' sizes and the long walks' plan.
@@ -1262,7 +1273,7 @@ void build_order(qw_batch *b) {
     std::vector<int> part(n);
     for (int64_t i = 0; i < n; ++i) {
         const WalkDesc &w = b->walks[i];
-        work[i] = walk_wave(b, w) || walk_long(b, w) ? w.T : walk_work(w);
+        work[i] = on_points(b, w) ? w.T : walk_work(w);
         part[i] = walk_wave(b, w) ? 0 : walk_long(b, w) ? kCfgK[w.cfg] : w.cfg < 0 ? 1002 : walk_slim(b, w) ? 1000 : 1001;
     }
     std::stable_sort(b->order.begin(), b->order.end(), [&](int32_t a, int32_t c) {
@@ -1295,8 +1306,8 @@ void build_order(qw_batch *b) {
         });
 }
 
-// device memory of the long walks' plan (build_order), and its tables; any earlier
-// plan's is released first
+// device memory of the long walks' plan (build_order), and its tables; what an earlier
+// plan left is released first
 hipError_t upload_long(qw_batch *b) {
     for (int k = 0; k < 2; ++k) {
         (void)hipFree(b->d_long_norms[k]);
@@ -1336,10 +1347,10 @@ hipError_t alloc_slim(qw_batch *b) {
 }
 
 // the largest ring the queue runs through the slot buffers
-int64_t queue_sites(const qw_batch *b, bool every) {
+int64_t queue_sites(const qw_batch *b) {
     int64_t m = 0;
     for (const auto &w : b->walks)
-        if (w.cfg >= 0 && (every || !(walk_wave(b, w) || walk_long(b, w)))) m = std::max<int64_t>(m, w.N);
+        if (w.cfg >= 0 && !on_points(b, w)) m = std::max<int64_t>(m, w.N);
     return m;
 }
 
@@ -1495,11 +1506,9 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
         const std::string dk = device_key();
         for (int bk = 0; bk < 3; ++bk) {
             auto it = cache.find(dk + "/" + std::to_string(prec) + "/" + std::to_string(bk));
-            if (it != cache.end()) b->bucket_cfg[bk] = it->second;
+            b->bucket_cfg[bk] = it != cache.end() ? it->second : kDefaultCfg[bk];
             if (o.tiled_variant > 0) b->bucket_cfg[bk] = o.tiled_variant - 1;
         }
-        for (auto &w : b->walks)
-            if (w.cfg >= 0) w.cfg = b->bucket_cfg[size_bucket(w.N)];
     }
     for (int64_t i = 0; i < n; ++i) b->walks[i].p_off = b->p_off[i];
     b->points = o.tiled_variant == 0;
@@ -1513,7 +1522,8 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
         }
         b->few_short = n_long > 0 && n_wave < kFewShort;
     }
-    b->slot_elems = queue_sites(b, false);
+    b->slot_elems = queue_sites(b);
+    assign_variants(b);
     build_order(b);
     if (upload_long(b) != hipSuccess) {
         // no room for every long walk's planes at once: one workgroup per walk
@@ -1523,7 +1533,8 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
             b->d_long[k] = nullptr;
         }
         b->points = false;
-        b->slot_elems = queue_sites(b, false);
+        b->slot_elems = queue_sites(b);
+        assign_variants(b);
         build_order(b);
         (void)upload_long(b);
     }
@@ -1665,38 +1676,15 @@ int walk_batch_info(qw_batch_t b, qw_batch_info *out) {
 int walk_batch_tune(qw_batch_t b, int32_t samples, int32_t save) {
     if (!b) return bfail(QW_EINVAL, "batch handle is NULL");
     if (samples < 1) samples = 8;
-    // the runs time the queue's kernel on every tiled walk: slot buffers for the largest
-    struct Slots {
-        qw_batch *b;
-        void *kept;
-        int64_t elems;
-        void restore() {
-            if (b->d_slots != kept) (void)hipFree(b->d_slots);
-            b->d_slots = kept;
-            b->slot_elems = elems;
-        }
-        ~Slots() { restore(); }
-    } slots{b, b->d_slots, b->slot_elems};
-    if (queue_sites(b, true) > b->slot_elems) {
-        void *p = nullptr;
-        const int64_t m = queue_sites(b, true);
-        if (hipMalloc(&p, (size_t)b->grid * 4 * m * (b->prec == QW_C128 ? 16 : 8)) != hipSuccess) {
-            (void)hipGetLastError();
-            return bfail(QW_ENOMEM, "hipMalloc for tuning failed");
-        }
-        b->d_slots = p;
-        b->slot_elems = m;
-    }
-    // per bucket: the tiled walks of the bucket, a spread sample by work
+    // per bucket: the tiled walks the queue runs (the others have no variant to choose)
     std::vector<int32_t> bucket_walks[3];
-    std::vector<int32_t> old_cfg(b->n);
-    const int old_bucket[3] = {b->bucket_cfg[0], b->bucket_cfg[1], b->bucket_cfg[2]};
-    for (int64_t i = 0; i < b->n; ++i) old_cfg[i] = b->walks[i].cfg;
     for (int64_t i = 0; i < b->n; ++i)
-        if (b->walks[i].cfg >= 0) bucket_walks[size_bucket(b->walks[i].N)].push_back((int32_t)i);
+        if (b->walks[i].cfg >= 0 && !on_points(b, b->walks[i])) bucket_walks[size_bucket(b->walks[i].N)].push_back((int32_t)i);
+    int chosen[3] = {b->bucket_cfg[0], b->bucket_cfg[1], b->bucket_cfg[2]};
     for (int bk = 0; bk < 3; ++bk) {
         auto &v = bucket_walks[bk];
         if (v.empty()) continue;
+        // (a spread sample by work)
         std::sort(v.begin(), v.end(), [&](int32_t a, int32_t c) { return walk_work(b->walks[a]) > walk_work(b->walks[c]); });
         std::vector<int32_t> pick;
         const int64_t ns = std::min<int64_t>(samples, (int64_t)v.size());
@@ -1754,33 +1742,38 @@ int walk_batch_tune(qw_batch_t b, int32_t samples, int32_t save) {
         }
         (void)hipFree(dw);
         (void)hipFree(dord);
-        b->bucket_cfg[bk] = best;
-        for (auto i : v) b->walks[i].cfg = best;
+        chosen[bk] = best;
     }
-    // the variants chosen decide which walks the slim kernel takes and the long walks'
-    // block depths: new order, and a new graph at the next run (the old one holds the
-    // old part sizes)
-    slots.restore();
-    build_order(b);
-    if (alloc_slim(b) != hipSuccess) {  // the batch stays as it was
-        for (int64_t i = 0; i < b->n; ++i) b->walks[i].cfg = old_cfg[i];
-        for (int bk = 0; bk < 3; ++bk) b->bucket_cfg[bk] = old_bucket[bk];
-        build_order(b);
-        return bfail(QW_ENOMEM, "hipMalloc of the slot buffers failed");
-    }
-    QB_HIP(upload_long(b), "the long walks' plan");
-    QB_HIP(hipMemcpyAsync(b->d_walks, b->walks.data(), sizeof(WalkDesc) * b->n, hipMemcpyHostToDevice, b->stream),
-           "upload of the walk table");
-    QB_HIP(hipMemcpyAsync(b->d_order, b->order.data(), sizeof(int32_t) * b->n, hipMemcpyHostToDevice, b->stream),
-           "upload of the queue order");
-    QB_HIP(hipStreamSynchronize(b->stream), "stream synchronise");
-    if (b->gexec) {
-        (void)hipGraphExecDestroy(b->gexec);
-        b->gexec = nullptr;
-    }
-    if (b->graph) {
-        (void)hipGraphDestroy(b->graph);
-        b->graph = nullptr;
+    if (!std::equal(chosen, chosen + 3, b->bucket_cfg)) {
+        // the variants decide which walks the slim kernel takes: new queue order (the walks
+        // on their live points keep their places and plan), and a new graph at the next run
+        // (the old one holds the old part sizes)
+        int old[3];
+        std::copy(b->bucket_cfg, b->bucket_cfg + 3, old);
+        auto take = [&](const int *cfg) {
+            std::copy(cfg, cfg + 3, b->bucket_cfg);
+            assign_variants(b);
+            build_order(b);
+        };
+        take(chosen);
+        if (alloc_slim(b) != hipSuccess) {  // the batch stays as it was
+            take(old);
+            return bfail(QW_ENOMEM, "hipMalloc of the slot buffers failed");
+        }
+        QB_HIP(hipStreamSynchronize(b->stream), "stream synchronise");
+        if (b->gexec) {
+            (void)hipGraphExecDestroy(b->gexec);
+            b->gexec = nullptr;
+        }
+        if (b->graph) {
+            (void)hipGraphDestroy(b->graph);
+            b->graph = nullptr;
+        }
+        QB_HIP(hipMemcpyAsync(b->d_walks, b->walks.data(), sizeof(WalkDesc) * b->n, hipMemcpyHostToDevice, b->stream),
+               "upload of the walk table");
+        QB_HIP(hipMemcpyAsync(b->d_order, b->order.data(), sizeof(int32_t) * b->n, hipMemcpyHostToDevice, b->stream),
+               "upload of the queue order");
+        QB_HIP(hipStreamSynchronize(b->stream), "stream synchronise");
     }
     if (save) {
         auto cache = read_cache();

@@ -39,3 +39,32 @@ def test_tuning_a_forced_variant(prec, variant, tmp_path, monkeypatch):
     assert np.array_equal(b.binned(), before[0])
     assert np.array_equal(b.moments(), before[1])
     b.destroy()
+
+
+def test_tuning_leaves_walks_on_live_points_alone(tmp_path, monkeypatch):
+    """Walks in registers and long ones are no kernel of the tuner's: neither its runs nor
+    a choice it saved for their size changes their launches or their values (complex64,
+    where each norm check may round), and a captured graph of them stays."""
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("QWALK_TUNE_CACHE", str(path))
+    walks = _walks(8, [4097] * 1100 + [9001, 20001], [400] * 1100 + [4100, 9000])
+    b = qwalk.Batch(*walks, prec=qwalk.QW_C64, nbins=64)
+    b.run()
+    before = b.binned(), b.moments(), list(b.info().bucket_cfg)
+    b.tune(samples=2, save=True)
+    assert b.info().graph == 1 and list(b.info().bucket_cfg) == before[2]
+    b.run()
+    assert np.array_equal(b.binned(), before[0]) and np.array_equal(b.moments(), before[1])
+    b.destroy()
+    # a choice saved for walks of the queue (both parities asked for)
+    f = qwalk.Batch(*_walks(9, [4097, 20001], [400, 900]), prec=qwalk.QW_C64, full_lattice=True)
+    f.tune(samples=1, save=True)
+    f.destroy()
+    lines = [ln.split() for ln in path.read_text().splitlines()]
+    assert len(lines) == 2
+    path.write_text("".join(f"{dev} {prec} {bucket} 0\n" for dev, prec, bucket, _ in lines))
+    c = qwalk.Batch(*walks, prec=qwalk.QW_C64, nbins=64)
+    assert list(c.info().bucket_cfg)[:2] == [0, 0]
+    c.run()
+    assert np.array_equal(c.binned(), before[0]) and np.array_equal(c.moments(), before[1])
+    c.destroy()
