@@ -1002,7 +1002,8 @@ struct qw_batch {
     // walks of one workgroup each, the next n_long advance together; the queue follows
     int64_t n_wave = 0, n_long = 0;
     bool few_short = false;  // the walks that fit registers are few: they join the long ones
-    bool points = true;  // false: a variant is forced, or the long walks' planes did not fit
+    bool points = true;    // false: a variant is forced
+    bool together = true;  // false: no room for the long walks' planes, they join the queue
     struct LongGroup {
         int32_t K;
         int64_t first, count;  // positions among the long walks, descending in T
@@ -1042,6 +1043,20 @@ struct qw_batch {
 
 namespace {
 
+// the long walks' planes, norms and tables
+void release_long(qw_batch *b) {
+    for (int k = 0; k < 2; ++k) {
+        (void)hipFree(b->d_long[k]);
+        (void)hipFree(b->d_long_norms[k]);
+        b->d_long[k] = nullptr;
+        b->d_long_norms[k] = nullptr;
+    }
+    (void)hipFree(b->d_long_off);
+    (void)hipFree(b->d_long_last);
+    b->d_long_off = nullptr;
+    b->d_long_last = nullptr;
+}
+
 void free_batch(qw_batch *b) {
     if (!b) return;
     if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
@@ -1051,12 +1066,7 @@ void free_batch(qw_batch *b) {
     (void)hipFree(b->d_queue);
     (void)hipFree(b->d_slots);
     (void)hipFree(b->d_slim_slots);
-    for (int k = 0; k < 2; ++k) {
-        (void)hipFree(b->d_long[k]);
-        (void)hipFree(b->d_long_norms[k]);
-    }
-    (void)hipFree(b->d_long_off);
-    (void)hipFree(b->d_long_last);
+    release_long(b);
     (void)hipFree(b->d_moments);
     (void)hipFree(b->d_bins);
     (void)hipFree(b->d_P);
@@ -1231,6 +1241,7 @@ bool walk_sub(const qw_batch *b, const WalkDesc &w) {
 // (at step t, t + 2 of its 2t + 3 offsets are live: counting half is low by at
 // most one site per step)
 bool on_points(const qw_batch *b, const WalkDesc &w);
+int64_t queue_sites(const qw_batch *b);
 double walk_performed(const qw_batch *b, const WalkDesc &w) {
     return on_points(b, w) || walk_sub(b, w) ? 0.5 * walk_work(w) : walk_work(w);
 }
@@ -1248,7 +1259,7 @@ bool walk_wave(const qw_batch *b, const WalkDesc &w) {
     return b->points && w.cfg >= 0 && w.rot && !b->full_lattice && !b->keep && !b->few_short && w.T <= kWaveMaxT;
 }
 bool walk_long(const qw_batch *b, const WalkDesc &w) {
-    return b->points && w.cfg >= 0 && w.rot && !b->full_lattice && w.T > 0 && !walk_wave(b, w);
+    return b->points && b->together && w.cfg >= 0 && w.rot && !b->full_lattice && w.T > 0 && !walk_wave(b, w);
 }
 
 bool on_points(const qw_batch *b, const WalkDesc &w) { return walk_wave(b, w) || walk_long(b, w); }
@@ -1306,22 +1317,19 @@ void build_order(qw_batch *b) {
         });
 }
 
-// device memory of the long walks' plan (build_order), and its tables; what an earlier
-// plan left is released first
+// bytes of the long walks' planes and partial norms
+size_t long_bytes(const qw_batch *b) {
+    return 2 * ((b->prec == QW_C128 ? 16 : 8) * (size_t)b->long_off[b->n_long] +
+                sizeof(double) * (size_t)b->long_tiles * b->n_long);
+}
+
+// device memory of the long walks' plan (build_order), and its tables; nothing is kept
+// where some of it fails
 hipError_t upload_long(qw_batch *b) {
-    for (int k = 0; k < 2; ++k) {
-        (void)hipFree(b->d_long_norms[k]);
-        b->d_long_norms[k] = nullptr;
-    }
-    (void)hipFree(b->d_long_off);
-    (void)hipFree(b->d_long_last);
-    b->d_long_off = nullptr;
-    b->d_long_last = nullptr;
-    if (b->n_long == 0) return hipSuccess;
     const size_t esz = b->prec == QW_C128 ? 16 : 8;
     hipError_t e = hipSuccess;
     for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-        if (!b->d_long[k]) e = hipMalloc(&b->d_long[k], esz * (size_t)b->long_off[b->n_long]);
+        e = hipMalloc(&b->d_long[k], esz * (size_t)b->long_off[b->n_long]);
         if (e == hipSuccess) e = hipMalloc((void **)&b->d_long_norms[k], sizeof(double) * (size_t)b->long_tiles * b->n_long);
     }
     if (e == hipSuccess) e = hipMalloc((void **)&b->d_long_off, sizeof(int64_t) * (b->n_long + 1));
@@ -1330,6 +1338,11 @@ hipError_t upload_long(qw_batch *b) {
         e = hipMemcpyAsync(b->d_long_off, b->long_off.data(), sizeof(int64_t) * (b->n_long + 1), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_long_last, b->long_last.data(), sizeof(int32_t) * b->n_long, hipMemcpyHostToDevice, b->stream);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipStreamSynchronize(b->stream);
+        release_long(b);
+    }
     return e;
 }
 
@@ -1344,6 +1357,22 @@ hipError_t alloc_slim(qw_batch *b) {
         b->d_slim_slots = nullptr;
     }
     return e;
+}
+
+// which kernel runs which walk, from the batch's options and `together`
+void plan(qw_batch *b) {
+    // a walk in registers lasts its steps in one wave (0.45 ms at T = 2000): a few of
+    // them cost a launch of that length, and nothing among the long walks' launches
+    int64_t n_wave = 0, n_long = 0;
+    b->few_short = false;
+    for (const auto &w : b->walks) {
+        n_wave += walk_wave(b, w);
+        n_long += walk_long(b, w);
+    }
+    b->few_short = n_long > 0 && n_wave < kFewShort;
+    b->slot_elems = queue_sites(b);
+    assign_variants(b);
+    build_order(b);
 }
 
 // the largest ring the queue runs through the slot buffers
@@ -1512,32 +1541,7 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
     }
     for (int64_t i = 0; i < n; ++i) b->walks[i].p_off = b->p_off[i];
     b->points = o.tiled_variant == 0;
-    {
-        // a walk in registers lasts its steps in one wave (0.45 ms at T = 2000): a few of
-        // them cost a launch of that length, and nothing among the long walks' launches
-        int64_t n_wave = 0, n_long = 0;
-        for (const auto &w : b->walks) {
-            n_wave += walk_wave(b, w);
-            n_long += walk_long(b, w);
-        }
-        b->few_short = n_long > 0 && n_wave < kFewShort;
-    }
-    b->slot_elems = queue_sites(b);
-    assign_variants(b);
-    build_order(b);
-    if (upload_long(b) != hipSuccess) {
-        // no room for every long walk's planes at once: one workgroup per walk
-        (void)hipGetLastError();
-        for (int k = 0; k < 2; ++k) {
-            (void)hipFree(b->d_long[k]);
-            b->d_long[k] = nullptr;
-        }
-        b->points = false;
-        b->slot_elems = queue_sites(b);
-        assign_variants(b);
-        build_order(b);
-        (void)upload_long(b);
-    }
+    plan(b);
     b->grid = persistent_grid(prec, n);
     b->grid_slim = persistent_grid(prec, n, true);
     const size_t esz = prec == QW_C128 ? 16 : 8;
@@ -1552,12 +1556,29 @@ int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const doubl
         }
         return true;
     };
+    auto queue_buffers = [&]() {
+        return alloc(&b->d_slots, (size_t)b->grid * 4 * b->slot_elems * esz) && (e = alloc_slim(b)) == hipSuccess;
+    };
     bool ok = alloc((void **)&b->d_walks, sizeof(WalkDesc) * n) && alloc((void **)&b->d_order, sizeof(int32_t) * n) &&
-              alloc((void **)&b->d_queue, 256) && alloc(&b->d_slots, (size_t)b->grid * 4 * b->slot_elems * esz) &&
-              (e = alloc_slim(b)) == hipSuccess &&
+              alloc((void **)&b->d_queue, 256) && queue_buffers() &&
               alloc((void **)&b->d_moments, sizeof(double) * 3 * n) &&
               (b->nbins == 0 || alloc((void **)&b->d_bins, sizeof(float) * b->nbins * n)) &&
               (!b->keep || alloc((void **)&b->d_P, sizeof(double) * off));
+    if (ok && b->n_long > 0) {
+        // The long walks' planes come last: they alone grow with the walks' number and
+        // length, and take at most half of what is free by then (the program's other memory,
+        // another batch).  Beyond that, those walks run in the queue, whose slots are one
+        // workgroup's.
+        size_t left = 0, total = 0;
+        if (hipMemGetInfo(&left, &total) != hipSuccess) (void)hipGetLastError();
+        if (long_bytes(b) > left / 2 || upload_long(b) != hipSuccess) {
+            b->together = false;
+            plan(b);
+            (void)hipFree(b->d_slots);
+            b->d_slots = nullptr;
+            ok = queue_buffers();
+        }
+    }
     if (!ok) {
         const std::string msg = hipGetErrorString(e);
         free_batch(b);

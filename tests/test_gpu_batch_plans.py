@@ -68,3 +68,33 @@ def test_tuning_leaves_walks_on_live_points_alone(tmp_path, monkeypatch):
     c.run()
     assert np.array_equal(c.binned(), before[0]) and np.array_equal(c.moments(), before[1])
     c.destroy()
+
+
+def test_planes_that_do_not_fit():
+    """Long walks whose planes take more of the card than their distributions leave: the
+    batch is created all the same (they run in the queue, whose memory does not grow with
+    them), and later allocations of this size still fit.  Nothing is run: it would last minutes."""
+    import torch
+    free = torch.cuda.mem_get_info()[0]
+    T, N = 500000, 1000001
+    # every P kept: 8 N a walk; planes: 2 x 2 (T + 1) complex64 = 16 N a walk
+    n = int(0.45 * free / (8 * N))
+    walks = (np.full(n, N), np.full(n, T), np.tile([[0.7, 0.2, 0.1]], (n, 1)), np.tile(inputs.PSI0_LR, (n, 1)))
+    b = qwalk.Batch(*walks, prec=qwalk.QW_C64, keep_probabilities=True)
+    left = torch.cuda.mem_get_info()[0]
+    b.destroy()
+    assert left > 0.2 * free
+    # without the distributions the planes fit, but not within half of the card
+    c = qwalk.Batch(*walks, prec=qwalk.QW_C64)
+    left = torch.cuda.mem_get_info()[0]
+    c.destroy()
+    assert left > 0.45 * free
+    # a smaller one takes them, and its walks are the queue's, bit for bit (no norm checks)
+    few = _walks(4, [20001, 30001], [5000, 9000])
+    res = []
+    for variant in (0, 4):
+        b = qwalk.Batch(*few, prec=qwalk.QW_C64, nbins=64, renorm_every=-1, tiled_variant=variant)
+        b.run()
+        res.append(b.binned())
+        b.destroy()
+    assert np.array_equal(*res)
