@@ -1253,13 +1253,16 @@ bool walk_slim(const qw_batch *b, const WalkDesc &w) {
 }
 
 // walks on their live points: rotation frame (the cone never wraps), both parities
-// not asked for; one workgroup in registers, or (too long for that, or with every P
-// kept) a block of steps at a time
+// not asked for; one workgroup in registers, or (too long for that) a block of steps at a
+// time.  Short walks whose P is kept, which the register kernel does not write, stay in the
+// queue (16384 rings of 4097 sites, T in [256, 2048]: complex64 3.8 ms against 4.9 among
+// the long walks, complex128 5.4 against 10.2; one ring 0.27 against 0.35).
+bool on_line(const qw_batch *b, const WalkDesc &w) { return b->points && w.cfg >= 0 && w.rot && !b->full_lattice; }
 bool walk_wave(const qw_batch *b, const WalkDesc &w) {
-    return b->points && w.cfg >= 0 && w.rot && !b->full_lattice && !b->keep && !b->few_short && w.T <= kWaveMaxT;
+    return on_line(b, w) && w.T <= kWaveMaxT && !b->keep && !b->few_short;
 }
 bool walk_long(const qw_batch *b, const WalkDesc &w) {
-    return b->points && b->together && w.cfg >= 0 && w.rot && !b->full_lattice && w.T > 0 && !walk_wave(b, w);
+    return on_line(b, w) && b->together && w.T > 0 && (w.T > kWaveMaxT || b->few_short);
 }
 
 bool on_points(const qw_batch *b, const WalkDesc &w) { return walk_wave(b, w) || walk_long(b, w); }
@@ -1361,15 +1364,15 @@ hipError_t alloc_slim(qw_batch *b) {
 
 // which kernel runs which walk, from the batch's options and `together`
 void plan(qw_batch *b) {
-    // a walk in registers lasts its steps in one wave (0.45 ms at T = 2000): a few of
+    // a short walk lasts its steps in one wave (0.25 ms at T = 2000): a few of
     // them cost a launch of that length, and nothing among the long walks' launches
-    int64_t n_wave = 0, n_long = 0;
+    int64_t n_short = 0, n_long = 0;
     b->few_short = false;
     for (const auto &w : b->walks) {
-        n_wave += walk_wave(b, w);
+        n_short += on_line(b, w) && w.T <= kWaveMaxT;
         n_long += walk_long(b, w);
     }
-    b->few_short = n_long > 0 && n_wave < kFewShort;
+    b->few_short = n_long > 0 && n_short < kFewShort;
     b->slot_elems = queue_sites(b);
     assign_variants(b);
     build_order(b);

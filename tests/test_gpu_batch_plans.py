@@ -98,3 +98,25 @@ def test_planes_that_do_not_fit():
         res.append(b.binned())
         b.destroy()
     assert np.array_equal(*res)
+
+
+def _ms(walks, **opts):
+    b = qwalk.Batch(*walks, **opts)
+    best = 1e9
+    for _ in range(6):
+        b.run()
+        best = min(best, b.info().last_run_ms)
+    b.destroy()
+    return best
+
+
+@pytest.mark.parametrize("prec", [qwalk.QW_C64, qwalk.QW_C128])
+@pytest.mark.parametrize("n", [16, 8192])
+def test_kept_distributions_of_short_walks(prec, n, tmp_path, monkeypatch):
+    """Short walks with every P kept last no longer than the queue's kernel takes for them
+    (variant 8, their default there; among the long walks it was 1.3 to 1.9 times that)."""
+    monkeypatch.setenv("QWALK_TUNE_CACHE", str(tmp_path / "tune.txt"))
+    rng = np.random.default_rng(2)
+    walks = (np.full(n, 4097), rng.integers(256, 2049, n), inputs.su2_angles(rng, n), np.tile(inputs.PSI0_LR, (n, 1)))
+    opts = dict(prec=prec, nbins=64, keep_probabilities=True)
+    assert _ms(walks, **opts) <= 1.15 * _ms(walks, tiled_variant=8, **opts)
