@@ -1003,7 +1003,7 @@ struct qw_batch {
     int64_t n_wave = 0, n_long = 0;
     bool few_short = false;  // the walks that fit registers are few: they join the long ones
     bool points = true;    // false: a variant is forced
-    bool together = true;  // false: no room for the long walks' planes, they join the queue
+    bool together = true;  // false: the long walks join the queue (long_pays, or no room for their planes)
     struct LongGroup {
         int32_t K;
         int64_t first, count;  // positions among the long walks, descending in T
@@ -1265,6 +1265,12 @@ bool walk_long(const qw_batch *b, const WalkDesc &w) {
     return on_line(b, w) && b->together && w.T > 0 && (w.T > kWaveMaxT || b->few_short);
 }
 
+// Steps per launch of a long walk.  Norms are checked after each launch's steps, so
+// with checks the depth is part of the results and stays the size's default.  Without
+// them nothing depends on it and 64 is the fastest at every size (256 rings of 9999 sites,
+// T = 4999, complex128: 16 4.3 ms, 32 2.4, 64 1.6; 512 of 99999: 707, 377, 215).
+int long_depth(const qw_batch *b, const WalkDesc &w) { return b->renorm_every > 0 ? kCfgK[w.cfg] : 64; }
+
 bool on_points(const qw_batch *b, const WalkDesc &w) { return walk_wave(b, w) || walk_long(b, w); }
 
 // Variants of the tiled walks: the tuned (or forced) one of their size for those the queue
@@ -1288,7 +1294,7 @@ void build_order(qw_batch *b) {
     for (int64_t i = 0; i < n; ++i) {
         const WalkDesc &w = b->walks[i];
         work[i] = on_points(b, w) ? w.T : walk_work(w);
-        part[i] = walk_wave(b, w) ? 0 : walk_long(b, w) ? kCfgK[w.cfg] : w.cfg < 0 ? 1002 : walk_slim(b, w) ? 1000 : 1001;
+        part[i] = walk_wave(b, w) ? 0 : walk_long(b, w) ? long_depth(b, w) : w.cfg < 0 ? 1002 : walk_slim(b, w) ? 1000 : 1001;
     }
     std::stable_sort(b->order.begin(), b->order.end(), [&](int32_t a, int32_t c) {
         if (part[a] != part[c]) return part[a] < part[c];
@@ -1362,6 +1368,28 @@ hipError_t alloc_slim(qw_batch *b) {
     return e;
 }
 
+// Whether the planned long walks end sooner together than in the queue.  Together: the
+// launches in series, each with its tiles of all walks.  In the queue: the longest walk in
+// one workgroup, or all of them over the chip.  Measured, ns: a launch 5.2 us at K = 32 and
+// 7.2 at 64, a tile 1.9 and 2.25 (complex128 4.2), a walk alone 60 T + 0.03 T^2, in a
+// full queue 0.00014 T^2 (complex128 0.00018).  Equal rings, together / in the queue: complex64
+// 64 of 9999 sites 0.98 / 1.07 ms, 256 of them 1.61 / 1.17, 1024 of 4999 1.25 / 0.86, of 20001
+// 10.4 / 16.3; complex128 256 of 4999 0.53 / 0.40, 1024 of 20001 18.7 / 17.2, 128 of 99999 54 / 91.
+bool long_pays(const qw_batch *b) {
+    const bool c128 = b->prec == QW_C128;
+    double together = 0.0, longest = 0.0, all = 0.0;
+    for (const auto &g : b->groups) {
+        const double launch = g.K == 32 ? 5200.0 : 7200.0, tile = c128 ? 4.2 : (g.K == 32 ? 1.9 : 2.25);
+        long_blocks(b, g, [&](int64_t, int64_t tiles, int64_t m) { together += launch + tile * (double)tiles * (double)m; });
+    }
+    for (int64_t p = 0; p < b->n_long; ++p) {
+        const double T = b->walks[b->order[b->n_wave + p]].T;
+        longest = std::max(longest, 60.0 * T + 0.03 * T * T);
+        all += (c128 ? 0.18e-3 : 0.14e-3) * T * T;
+    }
+    return together <= std::max(longest, all);
+}
+
 // which kernel runs which walk, from the batch's options and `together`
 void plan(qw_batch *b) {
     // a short walk lasts its steps in one wave (0.25 ms at T = 2000): a few of
@@ -1376,6 +1404,10 @@ void plan(qw_batch *b) {
     b->slot_elems = queue_sites(b);
     assign_variants(b);
     build_order(b);
+    if (b->n_long > 0 && !long_pays(b)) {
+        b->together = false;
+        plan(b);
+    }
 }
 
 // the largest ring the queue runs through the slot buffers

@@ -120,3 +120,16 @@ def test_kept_distributions_of_short_walks(prec, n, tmp_path, monkeypatch):
     walks = (np.full(n, 4097), rng.integers(256, 2049, n), inputs.su2_angles(rng, n), np.tile(inputs.PSI0_LR, (n, 1)))
     opts = dict(prec=prec, nbins=64, keep_probabilities=True)
     assert _ms(walks, **opts) <= 1.15 * _ms(walks, tiled_variant=8, **opts)
+
+
+@pytest.mark.parametrize("prec,n,N,T", [
+    (qwalk.QW_C64, 1024, 9999, 4999), (qwalk.QW_C64, 256, 4999, 2400), (qwalk.QW_C64, 1, 9999, 4999),
+    (qwalk.QW_C128, 2048, 9999, 3500), (qwalk.QW_C128, 256, 4999, 2400), (qwalk.QW_C128, 1, 9999, 4999),
+])
+def test_long_walks_take_the_faster_kernel(prec, n, N, T, tmp_path, monkeypatch):
+    """Many walks just past the register kernel's length, which fill the chip a workgroup
+    each, and one of them, which does not: never longer than the queue's kernel (variant 8)."""
+    monkeypatch.setenv("QWALK_TUNE_CACHE", str(tmp_path / "tune.txt"))
+    rng = np.random.default_rng(3)
+    walks = (np.full(n, N), np.full(n, T), inputs.su2_angles(rng, n), np.tile(inputs.PSI0_LR, (n, 1)))
+    assert _ms(walks, prec=prec, nbins=64) <= 1.15 * _ms(walks, prec=prec, nbins=64, tiled_variant=8)
