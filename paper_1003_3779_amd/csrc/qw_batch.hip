@@ -1103,6 +1103,13 @@ BatchArgs make_args(qw_batch *b, const WalkDesc *walks, const int32_t *order, in
     return A;
 }
 
+// A launch of 2^32 threads is refused: kernels with a workgroup (or more) per walk are
+// launched in parts of at most 2^31 threads, part(first walk, walks).
+template <typename F> void in_parts(int64_t walks, int64_t threads_per_walk, F part) {
+    const int64_t most = std::max<int64_t>(1, ((int64_t)1 << 31) / threads_per_walk);
+    for (int64_t first = 0; first < walks; first += most) part(first, std::min(most, walks - first));
+}
+
 // the slim kernel over queue positions [0, n_slim) (if any), then the general one
 // over the rest (if any); grid: the general kernel's workgroups
 hipError_t enqueue(qw_batch *b, const BatchArgs &A, int grid) {
@@ -1117,10 +1124,14 @@ hipError_t enqueue(qw_batch *b, const BatchArgs &A, int grid) {
             hipLaunchKernelGGL((k_batch<float, kMaxMC64, true>), dim3(gs), dim3(kBT), 0, b->stream, A);
     }
     if (A.links) {  // every walk is held whole
-        if (b->prec == QW_C128)
-            hipLaunchKernelGGL((k_links<double, kMaxMC128>), dim3((unsigned)A.n), dim3(kBT), 0, b->stream, A);
-        else
-            hipLaunchKernelGGL((k_links<float, kMaxMC64>), dim3((unsigned)A.n), dim3(kBT), 0, b->stream, A);
+        BatchArgs P = A;
+        in_parts(A.n, kBT, [&](int64_t first, int64_t walks) {
+            P.order = A.order + first;
+            if (b->prec == QW_C128)
+                hipLaunchKernelGGL((k_links<double, kMaxMC128>), dim3((unsigned)walks), dim3(kBT), 0, b->stream, P);
+            else
+                hipLaunchKernelGGL((k_links<float, kMaxMC64>), dim3((unsigned)walks), dim3(kBT), 0, b->stream, P);
+        });
     } else if (A.n > A.n_slim) {
         if (b->prec == QW_C128)
             hipLaunchKernelGGL((k_batch<double, kMaxMC128>), dim3(grid), dim3(kBT), 0, b->stream, A);
@@ -1141,6 +1152,15 @@ template <typename F> void long_blocks(const qw_batch *b, const qw_batch::LongGr
         const int tw = 64 * kLongM - g.K;
         visit(t0, (points + tw - 1) / tw, m);
     }
+}
+
+// the long walks from position `first` on
+LongArgs long_part(LongArgs L, int64_t first) {
+    L.order += first;
+    L.off += first;
+    L.last_tiles += first;
+    for (int k = 0; k < 2; ++k) L.norms[k] += first * L.max_tiles;
+    return L;
 }
 
 hipError_t enqueue_long(qw_batch *b, const BatchArgs &A) {
@@ -1164,9 +1184,13 @@ hipError_t enqueue_long(qw_batch *b, const BatchArgs &A) {
             L.t0 = (int32_t)t0;
             L.ntiles = (int32_t)tiles;
             L.prev_tiles = prev;
-            const unsigned blocks = (unsigned)((tiles + 3) / 4 * m);
-            if (b->prec == QW_C128) hipLaunchKernelGGL(k_ring_long<double>, dim3(blocks), dim3(256), 0, b->stream, L);
-            else hipLaunchKernelGGL(k_ring_long<float>, dim3(blocks), dim3(256), 0, b->stream, L);
+            const int64_t per = (tiles + 3) / 4;  // workgroups a walk
+            in_parts(m, per * 256, [&](int64_t first, int64_t walks) {
+                const LongArgs P = long_part(L, first);
+                const dim3 grid((unsigned)(per * walks));
+                if (b->prec == QW_C128) hipLaunchKernelGGL(k_ring_long<double>, grid, dim3(256), 0, b->stream, P);
+                else hipLaunchKernelGGL(k_ring_long<float>, grid, dim3(256), 0, b->stream, P);
+            });
             prev = (int)tiles;
             side ^= 1;
         });
@@ -1174,10 +1198,13 @@ hipError_t enqueue_long(qw_batch *b, const BatchArgs &A) {
             L.psi[k] = b->d_long[k];
             L.norms[k] = b->d_long_norms[k] + nb;
         }
-        if (b->prec == QW_C128)
-            hipLaunchKernelGGL(k_ring_long_end<double>, dim3((unsigned)g.count), dim3(kBT), 0, b->stream, L, A);
-        else
-            hipLaunchKernelGGL(k_ring_long_end<float>, dim3((unsigned)g.count), dim3(kBT), 0, b->stream, L, A);
+        in_parts(g.count, kBT, [&](int64_t first, int64_t walks) {
+            const LongArgs P = long_part(L, first);
+            if (b->prec == QW_C128)
+                hipLaunchKernelGGL(k_ring_long_end<double>, dim3((unsigned)walks), dim3(kBT), 0, b->stream, P, A);
+            else
+                hipLaunchKernelGGL(k_ring_long_end<float>, dim3((unsigned)walks), dim3(kBT), 0, b->stream, P, A);
+        });
     }
     return hipGetLastError();
 }
@@ -1189,14 +1216,16 @@ hipError_t enqueue_run(qw_batch *b) {
     hipError_t e = b->n_long > 0 ? enqueue_long(b, A) : hipSuccess;
     if (e == hipSuccess && b->n_wave > 0) {
         BatchArgs W = A;
-        W.order = b->d_order;
-        const dim3 grid((unsigned)b->n_wave);
-        if (b->prec == QW_C128)
-            hipLaunchKernelGGL((k_ring_wave<double, 1>), grid, dim3(128), wave_lds(1, 8, b->nbins), b->stream, W);
-        else if (b->n_wave < kFewWaves)
-            hipLaunchKernelGGL((k_ring_wave<float, 1>), grid, dim3(128), wave_lds(1, 4, b->nbins), b->stream, W);
-        else
-            hipLaunchKernelGGL((k_ring_wave<float, 2>), grid, dim3(64), wave_lds(2, 4, b->nbins), b->stream, W);
+        in_parts(b->n_wave, 128, [&](int64_t first, int64_t walks) {
+            W.order = b->d_order + first;
+            const dim3 grid((unsigned)walks);
+            if (b->prec == QW_C128)
+                hipLaunchKernelGGL((k_ring_wave<double, 1>), grid, dim3(128), wave_lds(1, 8, b->nbins), b->stream, W);
+            else if (b->n_wave < kFewWaves)
+                hipLaunchKernelGGL((k_ring_wave<float, 1>), grid, dim3(128), wave_lds(1, 4, b->nbins), b->stream, W);
+            else
+                hipLaunchKernelGGL((k_ring_wave<float, 2>), grid, dim3(64), wave_lds(2, 4, b->nbins), b->stream, W);
+        });
         e = hipGetLastError();
     }
     return e == hipSuccess ? enqueue(b, A, b->grid) : e;

@@ -133,3 +133,20 @@ def test_long_walks_take_the_faster_kernel(prec, n, N, T, tmp_path, monkeypatch)
     rng = np.random.default_rng(3)
     walks = (np.full(n, N), np.full(n, T), inputs.su2_angles(rng, n), np.tile(inputs.PSI0_LR, (n, 1)))
     assert _ms(walks, prec=prec, nbins=64) <= 1.15 * _ms(walks, prec=prec, nbins=64, tiled_variant=8)
+
+
+def test_more_realizations_than_one_launch_takes():
+    """2^23 + 1 walks with links, a workgroup of 512 threads each: 2^32 threads and more are not
+    one launch.  A segment of two sites: each walker steps right, the last three take no step."""
+    n = (1 << 23) + 1
+    N, T = np.full(n, 2), np.ones(n, dtype=np.int64)
+    T[-3:] = 0
+    ang, psi0 = np.zeros((n, 3)), np.zeros((n, 2), dtype=np.complex128)
+    psi0[:, 0] = 1.0
+    b = qwalk.Batch(N, T, ang, psi0, np.zeros(n, dtype=np.int64), prec=qwalk.QW_C64, walls=True)
+    b.run()
+    m = b.moments()
+    b.destroy()
+    # identity coin: site 0 -> site 1, offset 1
+    assert np.all(m[:, 0] == 1.0)
+    assert np.all(m[:-3, 1] == 1.0) and np.all(m[-3:, 1] == 0.0)
