@@ -1390,21 +1390,21 @@ int surr_predict(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, con
     memset(&ps, 0, sizeof ps);
     for (hipEvent_t &e : s->ev)
         if (!e) QS_HIP(hipEventCreate(&e), "hipEventCreate");
-    // 1. network on every walk: parameters up, features and forward on the device,
-    //    straight into the caller's device memory, or into HBM until the final copy.
-    //    Nothing waits for it before the re-check's distances are read: the host draws
+    // 1. network on every walk: parameters up, features and forward on the device; the
+    //    bins stay in HBM (w_out) until the final copy, so that a call that fails leaves
+    //    the caller's memory as it was, on the device too.  Nothing waits for it before the re-check's distances are read: the host draws
     //    the sample and sets up its plain walks meanwhile
     const int64_t npad = (n + 127) / 128 * 128;
     float *net = nullptr;
     {
         hipError_t e = room(s->w_xb, sizeof(bf16_t) * npad * kF);
         if (e == hipSuccess) e = room(s->w_t32, sizeof(int32_t) * npad);
-        if (e == hipSuccess && !o.out_on_device) e = room(s->w_out, sizeof(float) * n * kBins);
+        if (e == hipSuccess) e = room(s->w_out, sizeof(float) * n * kBins);
         if (e == hipSuccess) e = room(s->w_n, 8 * n);
         if (e == hipSuccess) e = room(s->w_t, 8 * n);
         if (e == hipSuccess) e = room(s->w_a, 24 * n);
         if (e == hipSuccess) e = room(s->w_p, 32 * n);
-        net = o.out_on_device ? out : (float *)s->w_out.p;
+        net = (float *)s->w_out.p;
         if (e == hipSuccess) e = hipEventRecord(s->ev[0], s->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(s->w_n.p, N, 8 * n, hipMemcpyHostToDevice, s->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(s->w_t.p, T, 8 * n, hipMemcpyHostToDevice, s->stream);
@@ -1529,9 +1529,10 @@ int surr_predict(qw_surr_t s, int64_t n, const int64_t *N, const int64_t *T, con
         QS_HIP(hipGetLastError(), "fallback scatter");
     }
     ps.fallback = (int64_t)fall.size();
-    // 5. the answers: one copy out of HBM (none when they were asked for on the device)
-    if (!o.out_on_device)
-        QS_HIP(hipMemcpyAsync(out, net, sizeof(float) * n * kBins, hipMemcpyDeviceToHost, s->stream), "copy of the bins");
+    // 5. the answers: one copy out of HBM
+    QS_HIP(hipMemcpyAsync(out, net, sizeof(float) * n * kBins,
+                          o.out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream),
+           "copy of the bins");
     QS_HIP(hipStreamSynchronize(s->stream), "stream synchronise");
     float ms = 0.0f;
     (void)hipEventElapsedTime(&ms, s->ev[0], s->ev[1]);
