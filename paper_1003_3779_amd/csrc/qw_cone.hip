@@ -651,18 +651,21 @@ __device__ __forceinline__ cv<R> cone_value(const R *__restrict__ a, const ConeV
 // whole-lattice pre-shift state a(y, c) = psi(y + e_c, c) (FULL = true)
 template <typename R, int TABLE, bool FULL>
 __global__ __launch_bounds__(256) void k_cone_expand(const R *__restrict__ a, ConeView V, void *__restrict__ out) {
-    for (int y = blockIdx.y; y < V.g.Ly; y += gridDim.y)
-        for (int x = blockIdx.x * 256 + threadIdx.x; x < V.g.Lx; x += gridDim.x * 256)
+    // sites in one run (a block a row leaves most lanes idle on narrow tori: 64 x 16384 sites 40 us)
+    const unsigned n = (unsigned)V.g.ps, Lx = (unsigned)V.g.Lx;
+    for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+        const int y = (int)(i / Lx), x = (int)(i - (unsigned)y * Lx);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int64_t o = (int64_t)c * V.g.ps + (int64_t)y * V.g.Lx + x;
-                if constexpr (FULL) {
-                    ((cv<R> *)out)[o] = cone_value<R, TABLE>(a, V, wrapi(x + V.g.ex[c], V.g.Lx), wrapi(y + V.g.ey[c], V.g.Ly), c);
-                } else {
-                    const cv<R> v = cone_value<R, TABLE>(a, V, x, y, c);
-                    ((double2 *)out)[o] = make_double2((double)v.x, (double)v.y);
-                }
+        for (int c = 0; c < 4; ++c) {
+            const int64_t o = (int64_t)c * V.g.ps + i;
+            if constexpr (FULL) {
+                ((cv<R> *)out)[o] = cone_value<R, TABLE>(a, V, wrapi(x + V.g.ex[c], V.g.Lx), wrapi(y + V.g.ey[c], V.g.Ly), c);
+            } else {
+                const cv<R> v = cone_value<R, TABLE>(a, V, x, y, c);
+                ((double2 *)out)[o] = make_double2((double)v.x, (double)v.y);
             }
+        }
+    }
 }
 
 // |psi|^2 of point (I, J), components ascending
@@ -681,6 +684,19 @@ __device__ __forceinline__ double point_prob(const R *__restrict__ a, const Cone
     return p;
 }
 
+// t = L / 2: the points at offset -t along an axis are the sites at +t; p plus theirs, for the
+// site at offset (dx, dy)
+template <typename R, int TABLE>
+__device__ __forceinline__ double seam_prob(const R *__restrict__ a, const ConeView &V, int dx, int dy, double p) {
+    const int t = V.t;
+    const bool ax = 2 * t == V.g.Lx && t > 0 && dx == t, ay = 2 * t == V.g.Ly && t > 0 && dy == t;
+    int I, J;
+    if (ax && cone_point<TABLE>(t, -t, dy, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
+    if (ay && cone_point<TABLE>(t, dx, -t, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
+    if (ax && ay && cone_point<TABLE>(t, -t, -t, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
+    return p;
+}
+
 // P over the whole lattice.  A block writes 64 x 64 sites.  With the axis-aligned
 // tables a lattice row runs along a diagonal of the square, so the block takes
 // its points in the square's order (coalesced loads) into an LDS tile and writes
@@ -691,13 +707,15 @@ struct alignas(8) Pair64 {
     double a, b;
 };
 template <typename R, int TABLE>
-__global__ __launch_bounds__(256) void k_cone_prob(const R *__restrict__ a, ConeView V, double *__restrict__ P, int skew) {
+__global__ __launch_bounds__(256) void k_cone_prob(const R *__restrict__ a, ConeView V, double *__restrict__ P, int skew, int ntx) {
     __shared__ double s[kPT * kPPitch];
     // the tile's first offset: offsets run over (-L/2, L/2]; the first column of tiles
     // starts skew sites early, on a 128-byte line of P
     const int Lx = V.g.Lx, Ly = V.g.Ly, t = V.t, tid = threadIdx.x;
-    const int bx = (int)blockIdx.x * kPT - (Lx - 1) / 2 - skew, by = (int)blockIdx.y * kPT - (Ly - 1) / 2;
-    const int lx0 = blockIdx.x == 0 ? skew : 0;                                  // tile inside the lattice
+    // (one grid dimension: a narrow torus may have more than 65535 rows of tiles)
+    const int ty = (int)(blockIdx.x / (unsigned)ntx), tx = (int)blockIdx.x - ty * ntx;
+    const int bx = tx * kPT - (Lx - 1) / 2 - skew, by = ty * kPT - (Ly - 1) / 2;
+    const int lx0 = tx == 0 ? skew : 0;                                  // tile inside the lattice
     const int nx = min(kPT, Lx / 2 - bx + 1), ny = min(kPT, Ly / 2 - by + 1);
     // distance of the tile from the start site along each axis
     const int gx = max(0, max(bx, -(bx + kPT - 1))), gy = max(0, max(by, -(by + kPT - 1)));
@@ -719,19 +737,9 @@ __global__ __launch_bounds__(256) void k_cone_prob(const R *__restrict__ a, Cone
         }
         __syncthreads();
     }
-    // t = L / 2: the points at offset -t are the sites at +t
-    const bool ax = 2 * t == Lx && t > 0, ay = 2 * t == Ly && t > 0;
     auto at = [&](int lx, int ly) -> double {
         if (empty) return 0.0;
-        const int dx = bx + lx, dy = by + ly;
-        double p = s[ly * kPPitch + lx];
-        if ((ax && dx == t) || (ay && dy == t)) {
-            int I, J;
-            if (ax && dx == t && cone_point<TABLE>(t, -t, dy, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
-            if (ay && dy == t && cone_point<TABLE>(t, dx, -t, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
-            if (ax && dx == t && ay && dy == t && cone_point<TABLE>(t, -t, -t, I, J)) p += point_prob<R, TABLE>(a, V, I, J);
-        }
-        return p;
+        return seam_prob<R, TABLE>(a, V, bx + lx, by + ly, s[ly * kPPitch + lx]);
     };
     for (int k = tid; k < kPT * kPT / 2; k += 256) {
         const int lx = 2 * (k % (kPT / 2)), ly = k / (kPT / 2);
@@ -967,9 +975,9 @@ hipError_t launch_cone_prob(int prec, int table, const void *state, const Cone &
     const ConeView V = cone_view(c, g);
     // the lattice column of the first offset, down to a line of 16
     int first = (int)(((int64_t)c.x0 - (g.Lx - 1) / 2 + g.Lx) % g.Lx);
-    const int skew = first % 16;
-    const dim3 grid((g.Lx + skew + kPT - 1) / kPT, (g.Ly + kPT - 1) / kPT);
-#define QW_CALL(R, TAB) hipLaunchKernelGGL((k_cone_prob<R, TAB>), grid, dim3(256), 0, s, (const R *)state, V, P, skew)
+    const int skew = first % 16, ntx = (g.Lx + skew + kPT - 1) / kPT;
+    const dim3 grid((unsigned)ntx * (unsigned)((g.Ly + kPT - 1) / kPT));
+#define QW_CALL(R, TAB) hipLaunchKernelGGL((k_cone_prob<R, TAB>), grid, dim3(256), 0, s, (const R *)state, V, P, skew, ntx)
     QW_CONE_DISPATCH(prec, table, QW_CALL);
 #undef QW_CALL
     return hipGetLastError();
@@ -995,7 +1003,7 @@ hipError_t launch_cone_renorm(int prec, void *state, const Cone &c, const Geom &
 hipError_t launch_cone_expand(int prec, int table, const void *state, const Cone &c, const Geom &g, void *out, bool full,
                               hipStream_t s) {
     const ConeView V = cone_view(c, g);
-    const dim3 grid(std::min((g.Lx + 255) / 256, 64), std::min(g.Ly, 16384));
+    const dim3 grid((unsigned)std::min<int64_t>((g.ps + 255) / 256, 1 << 16));
 #define QW_CALL(R, TAB)                                                                                                \
     do {                                                                                                               \
         if (full) hipLaunchKernelGGL((k_cone_expand<R, TAB, true>), grid, dim3(256), 0, s, (const R *)state, V, out);  \

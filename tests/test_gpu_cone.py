@@ -125,3 +125,24 @@ def test_cone_norm_checks_complex64():
     assert res[0][2] == res[1][2] == 290 // 64 and res[0][3] == res[1][3]
     assert np.max(np.abs(res[0][0] - res[1][0])) <= 2 * EPS[qwalk.QW_C64] * np.max(res[1][0])
     assert abs(res[0][1] - 1.0) <= 1e-6
+
+
+def test_narrow_torus_of_many_rows():
+    """More than 65535 rows of 64 x 64 tiles: past what a grid's second dimension takes."""
+    import torch
+    ext, x0 = (32, 65536 * 64 + 1), (30, 4194200)
+    psi0 = inputs.haar_state(np.random.default_rng(9), 4)
+    P = torch.empty(ext[1], ext[0], dtype=torch.float64, device="cuda")
+    w = qwalk.Walk(ext, inputs.PAIR, qwalk.GROVER, psi0, x0, prec=qwalk.QW_C64)
+    v = qwalk.Walk((32, 64), inputs.PAIR, qwalk.GROVER, psi0, (30, 40), prec=qwalk.QW_C64)   # the same cone on a torus that holds it
+    for T in (12, 8):     # on the square of live sites, and past it (the seam is at 16)
+        w.step(T)
+        v.step(T)
+        w.probabilities(out=P)
+        ref = v.probabilities()
+        rows = (np.arange(64) - 40 + x0[1]) % ext[1]
+        got = P[torch.as_tensor(rows, device="cuda")].cpu().numpy()
+        assert np.array_equal(got, ref)
+        assert float(P.sum()) == pytest.approx(float(ref.sum()), abs=1e-12)
+    w.destroy()
+    v.destroy()
