@@ -697,6 +697,26 @@ __device__ __forceinline__ double seam_prob(const R *__restrict__ a, const ConeV
     return p;
 }
 
+// k_cone_prob_sites on lattices of at most so many sites.  Tiles / sites, us, complex128, t = L / 4 and L / 2: 512^2
+// pair table 16.2 / 4.6 and 16.4 / 4.9, 2048^2 29.0 / 13.6 and 32.7 / 26.3, diagonal 14.6 / 13.8 and
+// 35.5 / 27.1; 4096^2 pair 41 / 46 and 152 / 126, diagonal 35 / 51 and 128 / 137.
+constexpr int64_t kProbSites = 1 << 22;
+
+// P over the whole lattice, a site per lane: small lattices, where the tiles below are too
+// few to hide their serial loads.  A wave takes 8 x 8 sites (a block 16 x 16): with the
+// axis-aligned tables their points are a patch of the square, not one long diagonal.
+template <typename R, int TABLE>
+__global__ __launch_bounds__(256) void k_cone_prob_sites(const R *__restrict__ a, ConeView V, double *__restrict__ P, int ntx) {
+    const int ty = (int)(blockIdx.x / (unsigned)ntx), tx = (int)blockIdx.x - ty * ntx, tid = threadIdx.x;
+    const int x = tx * 16 + ((tid >> 6) & 1) * 8 + (tid & 7), y = ty * 16 + (tid >> 7) * 8 + ((tid >> 3) & 7);
+    if (x >= V.g.Lx || y >= V.g.Ly) return;
+    const int dx = ring_off(x, V.x0, V.g.Lx), dy = ring_off(y, V.y0, V.g.Ly);
+    int I, J;
+    double p = 0.0;
+    if (cone_point<TABLE>(V.t, dx, dy, I, J)) p = point_prob<R, TABLE>(a, V, I, J);
+    P[(int64_t)y * V.g.Lx + x] = seam_prob<R, TABLE>(a, V, dx, dy, p);
+}
+
 // P over the whole lattice.  A block writes 64 x 64 sites.  With the axis-aligned
 // tables a lattice row runs along a diagonal of the square, so the block takes
 // its points in the square's order (coalesced loads) into an LDS tile and writes
@@ -973,6 +993,14 @@ hipError_t launch_cone_steps(int prec, int coin_impl, int table, bool inverse, c
 
 hipError_t launch_cone_prob(int prec, int table, const void *state, const Cone &c, const Geom &g, double *P, hipStream_t s) {
     const ConeView V = cone_view(c, g);
+    if (g.ps <= kProbSites) {
+        const int ntx = (g.Lx + 15) / 16;
+        const dim3 grid((unsigned)ntx * (unsigned)((g.Ly + 15) / 16));
+#define QW_CALL(R, TAB) hipLaunchKernelGGL((k_cone_prob_sites<R, TAB>), grid, dim3(256), 0, s, (const R *)state, V, P, ntx)
+        QW_CONE_DISPATCH(prec, table, QW_CALL);
+#undef QW_CALL
+        return hipGetLastError();
+    }
     // the lattice column of the first offset, down to a line of 16
     int first = (int)(((int64_t)c.x0 - (g.Lx - 1) / 2 + g.Lx) % g.Lx);
     const int skew = first % 16, ntx = (g.Lx + skew + kPT - 1) / kPT;

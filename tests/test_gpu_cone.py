@@ -146,3 +146,46 @@ def test_narrow_torus_of_many_rows():
         assert float(P.sum()) == pytest.approx(float(ref.sum()), abs=1e-12)
     w.destroy()
     v.destroy()
+
+
+@pytest.mark.parametrize("prec", [qwalk.QW_C128, qwalk.QW_C64])
+@pytest.mark.parametrize("table", ["PAIR", "DIAG"])
+@pytest.mark.parametrize("ext", [(64, 64), (50, 83), (2048, 2048), (2049, 2049), (64, 70001)])
+def test_cone_probabilities_on_both_kernels(prec, table, ext):
+    """P by sites (up to 2^22 of them) and by tiles (more, narrow tori among them), at the last steps
+    before the seam and on it: the squares of the state's amplitudes."""
+    L = min(ext)
+    psi0, x0 = inputs.haar_state(np.random.default_rng(8), 4), (L - 3, 5)
+    w = qwalk.Walk(ext, getattr(inputs, table), qwalk.GROVER, psi0, x0, prec=prec)
+    for T in (L // 2 - 1, 1):
+        w.step(T)
+        P, psi = w.probabilities(), w.get_state()
+        # sums of eight squares, in another order
+        assert np.max(np.abs(P - np.sum(psi.real ** 2 + psi.imag ** 2, axis=0))) <= 8 * EPS[qwalk.QW_C128]
+        assert abs(P.sum() - 1.0) <= (1e-12 if prec == qwalk.QW_C128 else 1e-5)
+    w.destroy()
+
+
+def test_small_lattices_are_not_slower_than_the_whole_lattice():
+    """P of a 512^2 walk, again and again: on the square it lasts no longer than on the whole
+    lattice (a fill and a kernel; by tiles it was 1.9 times that)."""
+    import time
+    import torch
+    psi0 = inputs.haar_state(np.random.default_rng(7), 4)
+    P = torch.empty(512, 512, dtype=torch.float64, device="cuda")
+    best = []
+    for opts in ({}, {"stream_kernel": 1}):
+        w = qwalk.Walk((512, 512), inputs.PAIR, qwalk.GROVER, psi0, (256, 256))
+        w.set_options(**opts)
+        w.step(128)
+        ts = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(200):
+                w.probabilities(out=P)
+            torch.cuda.synchronize()
+            ts.append(time.perf_counter() - t0)
+        best.append(min(ts))
+        w.destroy()
+    assert best[0] <= 1.2 * best[1]
