@@ -16,7 +16,9 @@
 // 2 t <= Lx and 2 t <= Ly no two of its points are the same site (t = L / 2 apart,
 // where the outermost points meet in pairs that no component shares).  Every live
 // amplitude is the same expression as in the kernels of the whole lattice
-// (bitwise equal); the others are exact zeros there and absent here.
+// (bitwise equal, but for complex128 numbers that pass below 2^-1022: ConeArgs::marks
+// are kept for complex64 alone, 2 % of a 4096^2 walk); the others are exact zeros there
+// and absent here.
 #include "qw_internal.h"
 
 #include <hip/hip_ext.h>

@@ -189,3 +189,57 @@ def test_small_lattices_are_not_slower_than_the_whole_lattice():
         best.append(min(ts))
         w.destroy()
     assert best[0] <= 1.2 * best[1]
+
+
+# from side 700 on a launch takes up to 32 steps in four stages.  Whole launches, and ones of 17 to
+# 31 steps (later stages pass rows through); complex64 groups of 12 steps end inside a stage;
+# strips and segments with remainders on both axes.
+DEEP = (2300, 2111)
+
+
+def _deep(table, kind, prec, plan, **opts):
+    import torch
+    w = qwalk.Walk(DEEP, getattr(inputs, table), kind, inputs.haar_state(np.random.default_rng([12, kind]), 4), (2290, 1000),
+                   prec=prec)
+    w.set_options(renorm_every=0, **opts)
+    for n in plan:
+        w.step(n)
+    psi = torch.empty(4, DEEP[1], DEEP[0], dtype=torch.complex128, device="cuda")
+    w.get_state(out=psi)
+    n = w.norm()
+    w.destroy()
+    return psi, n
+
+
+@pytest.mark.parametrize("table", ["PAIR", "EQ8", "DIAG"])
+@pytest.mark.parametrize("kind", [qwalk.GROVER, qwalk.HADAMARD2])
+@pytest.mark.parametrize("prec,opts", [(qwalk.QW_C128, {}), (qwalk.QW_C64, {}), (qwalk.QW_C64, {"block_depth": 12})])
+def test_four_stage_launches_bitwise(table, kind, prec, opts):
+    """complex64: bit for bit, subnormal numbers too.  complex128 multiplies the levels' powers of two back
+    at the end of a launch, wherever the whole lattice's launches end: numbers below 2^-1022 (the fronts from t = 1022
+    on) round at other steps, each launch by 2^-1075 a value or sqrt(2300 2111 8) 2^-1075 in the 2-norm, which
+    the steps keep, so 66 launches by less than 2^-1055; every value above 2^-1002 agrees bit for bit."""
+    import torch
+    for plan in ([1055], [701, 32, 17, 1], [1000, 31, 24]):
+        psi, n = _deep(table, kind, prec, plan, **opts)
+        ref, nr = _deep(table, kind, prec, plan, stream_kernel=1, **opts)
+        assert float((torch.view_as_real(psi) - torch.view_as_real(ref)).abs().max()) <= (2.0 ** -1055 if prec == qwalk.QW_C128 else 0.0), plan
+        assert abs(n - nr) <= 1e-12
+
+
+@pytest.mark.parametrize("kind", [qwalk.GROVER, qwalk.HADAMARD2])
+def test_four_stage_norm_checks(kind):
+    """Norm sums left by launches of 32 steps: complex64 checks every 64 steps up to t = 1050.  A rescale whose
+    norm was summed in another order rounds within 2^-24 of the state, so P differs by at most
+    2 sqrt(max P) 2^-24 for each of the 16 checks."""
+    res = []
+    for opts in ({}, {"stream_kernel": 1}):
+        w = qwalk.Walk(DEEP, inputs.PAIR, kind, inputs.haar_state(np.random.default_rng(13), 4), (3, 4), prec=qwalk.QW_C64)
+        w.set_options(**opts)
+        w.step(1050)
+        st = w.stats()
+        res.append((w.probabilities(), st.renorm_checks, st.renorms, st.last_norm))
+        w.destroy()
+    assert res[0][1] == res[1][1] == 16 and res[0][2] == res[1][2]
+    assert abs(res[0][3] - res[1][3]) <= 16 * 2.0 ** -23
+    assert np.max(np.abs(res[0][0] - res[1][0])) <= 16 * 2 * np.sqrt(np.max(res[1][0])) * EPS[qwalk.QW_C64]
