@@ -155,8 +155,9 @@ typedef struct {
     double bytes_written;   /* HBM bytes the launches wrote */
     double updates;         /* site*coin updates of the walk those launches advanced */
     double min_bytes;       /* the least those launches must move: each launch's input
-                               (light-cone box of the state it starts from) read once and
-                               its output box written once, no halo re-reads */
+                               (light-cone box, or square of live sites, of the state it
+                               starts from) read once and its output written once, no halo
+                               re-reads */
 } qw_kernel_profile;
 
 typedef struct {
@@ -165,7 +166,8 @@ typedef struct {
     int64_t renorms;          /* rescalings applied (read back from the device) */
     double last_norm;         /* norm seen by the latest check (read back from the device) */
     int64_t launches;         /* kernel launches issued by walk_step / walk_step_inverse */
-    int64_t updates;          /* site*coin updates performed (window-limited) */
+    int64_t updates;          /* site*coin updates performed (of the window, or of the live sites
+                                 alone where the walk is held on those) */
 } qw_stats;
 
 /* Create a walk in the state |x0> (x) psi0 at t = 0.
@@ -310,7 +312,7 @@ int walk_run_noalloc(const qw_lattice *lattice, const qw_coin *coin, const doubl
                      void *state_a, void *state_b, int64_t T, double *P_out, double *norm_out);
 
 /* ------------------------------------------------------------------------
- * Batches of independent ring walks in one persistent launch.
+ * Batches of independent ring walks, one graph replay per run.
  *
  * Walk i runs on a ring of N[i] sites with the SU(2) coin of angles
  * (theta, phi, chi) = angles[3i..3i+2], start coin state psi0[4i..4i+3]
@@ -323,7 +325,8 @@ int walk_run_noalloc(const qw_lattice *lattice, const qw_coin *coin, const doubl
  * and h; h = nbins/2, w = floor((N-1)/2 / h)) and optionally every full P(x).
  * Short walks whose cone does not meet itself run in registers, long ones together,
  * a block of steps per launch, walks with links or walls a workgroup each, the rest
- * (and forced variants) longest-first from an atomic queue; a run is one replay of a
+ * (forced variants, short walks whose P is kept, long ones where the queue ends sooner)
+ * longest-first from an atomic queue; a run is one replay of a
  * captured hipGraph of these kernels.  With stream NULL
  * the batch uses a private stream and calls return only when done.
  * ------------------------------------------------------------------------ */
@@ -342,7 +345,7 @@ typedef struct {
     int32_t renorm_every;        /* fp64 norm check (rescale by 1/sqrt(n) when |n - 1| > 1e-7):
                                     0 = default (every 64 steps in QW_C64, never in QW_C128),
                                     > 0 = every so many steps (rings held whole; longer rings
-                                    check after every K-step block), < 0 = never */
+                                    check after every block of steps), < 0 = never */
     int32_t whole_max_sites;     /* which rings are held whole in one workgroup's registers
                                     (all N sites every step; at most 4608 sites in QW_C64,
                                     2048 in QW_C128) instead of running tiled over their light
@@ -370,7 +373,7 @@ typedef struct {
 
 typedef struct {
     int64_t n;                 /* walks */
-    int32_t grid;              /* persistent workgroups */
+    int32_t grid;              /* persistent workgroups of the queue's kernel */
     int32_t graph;             /* 1 once a hipGraph has been captured */
     int64_t whole_ring_walks;  /* walks held whole in one workgroup's registers */
     double est_updates;        /* site*coin updates one run performs (light cone, or its live
@@ -385,8 +388,9 @@ typedef struct {
                                   whole rings in full): the updates of the method's window */
 } qw_batch_info;
 
-/* Validate and upload the walk table; allocate per-walk outputs and the slot
- * buffers of the persistent workgroups.  N, T: n int64; angles: 3n doubles;
+/* Validate and upload the walk table; allocate per-walk outputs, the slot
+ * buffers of the queue's workgroups and, within half of the memory left free, the
+ * planes of the long walks that advance together.  N, T: n int64; angles: 3n doubles;
  * psi0: 4n doubles; x0: n int64 or NULL; opts may be NULL (all zero). */
 int walk_batch_create(int64_t n, const int64_t *N, const int64_t *T, const double *angles,
                       const double *psi0, const int64_t *x0, int32_t prec,

@@ -1,8 +1,12 @@
 // qw_batch.hip -- many independent ring walks (each with its own N, T, SU(2)
-// coin, start coin state and start site) in one persistent launch.
+// coin, start coin state and start site) in one run, a replay of a captured graph.
 //
-// Each workgroup (512 threads, 8 waves) pops walks from an atomic queue that
-// the host ordered longest-first (LPT) and runs each popped walk to the end:
+// Walks whose cone never wraps run on the points they can reach (qw_rings.h): short ones in
+// registers, long ones together, a block of steps per launch.  Walks with broken links
+// or walls take a workgroup each (k_links).  The others, and those the plan (plan()) finds
+// faster there, share one persistent launch: each workgroup (512 threads, 8 waves) pops walks
+// from an atomic queue that the host ordered longest-first (LPT) and runs each popped
+// walk to the end:
 //  * a ring of N <= 512*M_max sites is held whole in registers (M sites per
 //    thread), neighbour values cross thread boundaries through LDS with one
 //    barrier per step -- no memory traffic inside the walk;
@@ -14,7 +18,7 @@
 //    bins and, optionally, the full distribution.
 // The walk's steps are the ring case of U = S (I (x) C) (Sec. 2.1, Eq. 2;
 // component 0 moves +1, component 1 moves -1, as in the segment kernel of
-// Fig. 2).  The grid exits once the queue is empty: every wave reaches the
+// Fig. 2).  The queue's grid exits once the queue is empty: every wave reaches the
 // exit test after its last walk.
 #include "qwalk.h"
 #include "qw_device.h"

@@ -35,8 +35,10 @@ constexpr int kConeWaves = 1;     // waves per SIMD a one-stage launch aims at (
 // launches of more than kK steps: levels a stage, stages, rows a group.  Four stages of
 // 8 levels, 4096^2 Grover complex128 / 16384^2 H (x) H complex64: 5.71 / 27.9 ms a
 // walk; two of 16 5.74 / 29.3, four with twice the columns a lane and one row a group 6.8 /
-// 35.4, one-stage launches of 16 throughout 6.98 / 29.9.  Waves per SIMD: 2 (1: 6.6 / 33.5,
-// 3: 6.0 / 29.2)
+// 35.4, one-stage launches of 16 throughout 6.98 / 29.9.  Segments are cut for two waves per SIMD
+// (for one: 6.6 / 33.5; for three, of which 182 to 196 registers leave two resident: 6.0 / 29.2).
+// Counted: complex128 issues on 58 % of the cycles and its waves wait 36 % of theirs (a barrier
+// every two rows, two waves to hide it), complex64 80 % and 26 %.
 constexpr int kDeepKL = 8, kDeepNS = 4, kDeepNR = 2;
 template <typename R> constexpr int kDeepM = sizeof(R) == 8 ? 2 : 4;  // and columns a lane
 constexpr int kDeepSide = 700;  // squares from this side on take them (400 and 1200: the same within 1 %)

@@ -265,7 +265,8 @@ template <typename R, int NP> __global__ __launch_bounds__(64 * (3 - NP), sizeof
 }
 
 // ---------------------------------------------------------------- long walks
-// All long walks of a batch advance together, a block of K steps per launch: their
+// The long walks of a batch advance together, a block of K steps per launch (where that ends
+// sooner than the queue: long_pays in qw_batch.hip): their
 // cones have the same size at the same time, so a launch is (tiles of that cone) x
 // (walks still running, longest first) waves, and the largest walks, which alone
 // decided when a batch of one workgroup per walk ended, spread over the whole chip.  A

@@ -270,7 +270,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &g, int bl, int gx, bf1
     }
 }
 
-// out[c][r] = in[r][c] (bf16, R x C -> C x R), 32 x 32 tiles through LDS
+// fp32 to bf16 (the parameters' mirror that the products read)
 __global__ void k_f32_to_bf16(const float *__restrict__ in, bf16_t *__restrict__ out, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         out[i] = f2bf(in[i]);
