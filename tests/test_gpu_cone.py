@@ -173,20 +173,20 @@ def test_small_lattices_are_not_slower_than_the_whole_lattice():
     import torch
     psi0 = inputs.haar_state(np.random.default_rng(7), 4)
     P = torch.empty(512, 512, dtype=torch.float64, device="cuda")
-    best = []
+    ws, best = [], [1e9, 1e9]
     for opts in ({}, {"stream_kernel": 1}):
-        w = qwalk.Walk((512, 512), inputs.PAIR, qwalk.GROVER, psi0, (256, 256))
-        w.set_options(**opts)
-        w.step(128)
-        ts = []
-        for _ in range(8):
+        ws.append(qwalk.Walk((512, 512), inputs.PAIR, qwalk.GROVER, psi0, (256, 256)))
+        ws[-1].set_options(**opts)
+        ws[-1].step(128)
+    for _ in range(8):
+        for i, w in enumerate(ws):
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             for _ in range(200):
                 w.probabilities(out=P)
             torch.cuda.synchronize()
-            ts.append(time.perf_counter() - t0)
-        best.append(min(ts))
+            best[i] = min(best[i], time.perf_counter() - t0)
+    for w in ws:
         w.destroy()
     assert best[0] <= 1.2 * best[1]
 
